@@ -137,13 +137,16 @@ iso_status iso_batch_create(const iso_mesh *const *meshes, int32_t n, const iso_
     if (hipGetDevice(&dev) != hipSuccess) return fail(ISO_EDEVICE, "no HIP device");
     int64_t N = 0, F = 0, K = 0, S = 0, P = 0, NF = 0;
     int64_t NB = 0, NBV = 0, NBF = 0, NBL = 0;  // general polyhedra: cells, points, faces, loop entries
-    int32_t W = 1, big_face_pts = 0;
-    bool generic = false, any_big = false, all_big = true, narrow = false, wide = false;
+    int32_t W = 1, big_face_pts = 0, sten_n = 0;
+    bool generic = false, any_big = false, all_big = true, narrow = false, wide = false, any_box = false, all_box = true;
     for (int32_t i = 0; i < n; ++i) {
         const iso_mesh *m = meshes[i];
         if (!m) return fail(ISO_EINVAL, "null mesh in the ensemble");
         if (m->device != dev) return fail(ISO_EINVAL, "ensemble members must live on the current device");
         generic = generic || m->generic;
+        any_box = any_box || m->dev.box;
+        all_box = all_box && m->dev.box;
+        sten_n = std::max(sten_n, m->dev.sten_n);
         if (m->dev.cbig) {
             any_big = true;
             big_face_pts = std::max(big_face_pts, m->dev.big_face_pts);
@@ -193,6 +196,14 @@ iso_status iso_batch_create(const iso_mesh *const *meshes, int32_t n, const iso_
         return fail(ISO_ENOMEM, "ensemble mesh allocation failed");
     }
     std::vector<std::vector<int32_t>> hex_loops;  // host staging, alive until the copies are done
+    // members of rectangular hexahedra: their extents and stencil tables (the other members' parts are
+    // not read)
+    double *bext = nullptr, *sten_w = nullptr;
+    int32_t *sten_cell = nullptr;
+    if (any_box && (!dev_alloc(u, &bext, 3 * N) || !dev_alloc(u, &sten_w, (int64_t)sten_n * K) || !dev_alloc(u, &sten_cell, (int64_t)sten_n * K))) {
+        iso_batch_destroy(b);
+        return fail(ISO_ENOMEM, "ensemble mesh allocation failed");
+    }
     // general polyhedra: their point, face and loop arrays concatenated, indices offset
     int32_t *cbig = nullptr, *bv_ptr = nullptr, *bv_cls = nullptr, *bf_ptr = nullptr, *bf_face = nullptr,
             *bf_planar = nullptr, *bl_ptr = nullptr, *bl_vtx = nullptr;
@@ -239,6 +250,11 @@ iso_status iso_batch_create(const iso_mesh *const *meshes, int32_t n, const iso_
         ok(hipMemcpyAsync(vol + co, md.vol, nc * sizeof(double), hipMemcpyDeviceToDevice, s));
         ok(hipMemcpyAsync(ccen + 3 * co, md.ccen, 3 * nc * sizeof(double), hipMemcpyDeviceToDevice, s));
         ok(hipMemcpyAsync(cflags + co, md.cflags, nc * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
+        if (md.box) {
+            ok(hipMemcpyAsync(bext + 3 * co, md.bext, 3 * nc * sizeof(double), hipMemcpyDeviceToDevice, s));
+            ok(launch_stencil_copy(md.sten_cell, md.sten_w, md.sten_n, sten_cell + sten_n * ko, sten_w + sten_n * ko, sten_n,
+                                   m->n_classes, (int32_t)co, s));
+        }
         ok(launch_offset_copy(md.cpt, cpt + 8 * co, 8 * nc, 0, (int32_t)ko, 0, s));
         for (int k = 0; k < W; ++k) {
             int32_t *df = sface + (size_t)k * N + co, *dn = snbr + (size_t)k * N + co;
@@ -345,6 +361,9 @@ iso_status iso_batch_create(const iso_mesh *const *meshes, int32_t n, const iso_
     d.cflags = cflags; d.st_ptr = st_ptr; d.st_cell = st_cell; d.st_w = st_w; d.patch_alpha = palpha;
     d.ccen = ccen;
     d.cloop = cloop;
+    d.box = all_box ? 1 : (any_box ? 2 : 0);
+    d.bext = bext;
+    d.sten_n = sten_n; d.sten_cell = sten_cell; d.sten_w = sten_w;
     d.n_dom = n; d.dom_off = dom_off;
     if (words) {
         d.slot_nar = reinterpret_cast<const uint32_t *>(snar);

@@ -139,6 +139,18 @@ __device__ __forceinline__ double grp_sum(double v) {
 __device__ __forceinline__ D3 grp_sum3(D3 v) { return D3{grp_sum(v.x), grp_sum(v.y), grp_sum(v.z)}; }
 __device__ __forceinline__ double grp_get(double v, int src) { return __shfl(v, src, 8); }
 
+// The flux of face f and the velocity of cell c; with a second time level (outer iterations,
+// Crank-Nicolson) their averages, formed as they are read.
+template <bool kAvg>
+__device__ __forceinline__ double flux_at(const double *phi, const double *phi1, int32_t f) {
+    if constexpr (kAvg) return 0.5 * (phi[f] + phi1[f]);
+    else return phi[f];
+}
+__device__ __forceinline__ D3 vel_at(const double *U, const double *U1, int32_t c, size_t n) {
+    if (U1) return D3{0.5 * (U[c] + U1[c]), 0.5 * (U[n + c] + U1[n + c]), 0.5 * (U[2 * n + c] + U1[2 * n + c])};
+    return D3{U[c], U[n + c], U[2 * n + c]};
+}
+
 // Append `count` entries per lane to a device-wide list: one atomic per wave.  Returns the index of
 // this lane's first entry.  Every active lane of the wave must call it (count may be 0).
 __device__ __forceinline__ int wave_append(int count, int32_t *counter) {

@@ -36,6 +36,10 @@ constexpr int32_t hex_loop_word(int k) {
     return w;
 }
 
+// Cell flag of a mesh made of rectangular hexahedra only, edges exactly along the coordinate axes:
+// its interface cells take the kernel of box.hip.  Bits 13 + 3i, 14 + 3i hold the axis of canonical
+// edge i (vertex 0 to 1, 3 and 4 for i = 0, 1, 2), bit 15 + 3i is set when it runs downwards.
+constexpr int32_t kCellBox = 1 << 12;
 // Device view of a mesh, passed to kernels by value.
 struct DevMesh {
     int32_t n_cells = 0, n_faces = 0, n_classes = 0, W = 0, n_patches = 0;
@@ -57,7 +61,8 @@ struct DevMesh {
     const uint32_t *slot_nar = nullptr;
     uint32_t nar_S = 0;
     const int32_t *lface = nullptr;      // [6*n_cells] packed flux face of each canonical face, or kEmpty
-    const int32_t *cflags = nullptr;     // [n_cells] bit k: canonical face k is planar
+    const int32_t *cflags = nullptr;     // [n_cells] bit k: canonical face k is planar; kCellBox and the
+                                         // bits above it: see there
     const int32_t *st_ptr = nullptr;     // [n_classes+1] vertex stencils
     const int32_t *st_cell = nullptr;
     const double *st_w = nullptr;        // normalised inverse-distance weights
@@ -86,6 +91,14 @@ struct DevMesh {
     int32_t big_class = -1;              // 2: polyhedra of both instantiation classes (cflags bit
                                          // 11: the mesh they come from has faces of more than 4
                                          // points), each launch taking its own class
+    int32_t box = 0;                     // cells with kCellBox: 0 none, 1 all, 2 some
+    const double *bext = nullptr;        // [3*n_cells] their lengths along canonical edges 0, 1, 2
+    // the vertex stencils of meshes of rectangular hexahedra at a fixed width, [n_classes][sten_n] (sten_n
+    // is 4 or 8; a shorter stencil repeats its first cell with weight 0): a vertex's entries are one
+    // run found without st_ptr, read in 16-byte loads
+    int32_t sten_n = 0;
+    const int32_t *sten_cell = nullptr;
+    const double *sten_w = nullptr;
     // ensembles: cells [dom_off[d], dom_off[d+1]) belong to member d, whose time step is
     // dt_dom[d] (n_dom = 0 for a single mesh: one scalar time step)
     int32_t n_dom = 0;
@@ -214,6 +227,27 @@ struct AdjInputs {
     double *abar, *phibar;     // adjoints out
 };
 
+// The interface-cell kernels (kernels.hip, box.hip).
+struct SurfArgs {
+    DevMesh m;
+    const double *alpha, *phi, *U;
+    double dt;
+    const double *dt_dom;
+    double eps, flat_tol;
+    int32_t max_rounds;
+    const int32_t *list;
+    int32_t *counters;
+    int32_t cap;
+    double *dvs;
+    int want_stats;
+    iso_trace tr;
+    const double *phi1, *U1;  // second time level, or nullptr
+    double root_tol;          // stop the isovalue search at |V_sub/V - alpha| <= root_tol (0: round-off)
+};
+
+// box.hip: the rectangular hexahedra (cflags bit 12) of the list
+hipError_t launch_surface_box(const SurfArgs &a, const LaunchCfg &cfg, int us_mode, hipStream_t s);
+
 // kernels.hip
 // ev: nullptr, or 5 events recorded before each of the 4 kernels and after the last
 hipError_t launch_step(const DevMesh &m, const DevWork &w, const Params &p, const StepArgs &a,
@@ -223,6 +257,9 @@ hipError_t launch_step(const DevMesh &m, const DevWork &w, const Params &p, cons
 // v + off1, else -1 - (-1 - v + off2).  src == nullptr fills dst with off1.
 hipError_t launch_offset_copy(const int32_t *src, int32_t *dst, int64_t n, int mode, int32_t off1, int32_t off2,
                               hipStream_t s);
+// dst stencils (nd entries each) from src's (ns <= nd), cells offset by off, as DevMesh::sten_cell
+hipError_t launch_stencil_copy(const int32_t *cell, const double *w, int32_t ns, int32_t *dcell, double *dw, int32_t nd,
+                               int64_t n, int32_t off, hipStream_t s);
 hipError_t launch_copy_f64(const double *src, double *dst, int64_t n, hipStream_t s);
 // m.slot_pair from m.slot_face and m.slot_nbr (pairs: [n_cells * W] device array)
 hipError_t launch_slot_pairs(const DevMesh &m, int2 *pairs, hipStream_t s);

@@ -10,8 +10,9 @@
 //                  (one isoface edge per lane), Illinois otherwise.  It builds the isoface, and
 //                  lane k integrates the submerged fraction of face k over the step when it is an
 //                  outflow face (Eqs. tv .. intaplus) -> dV (each face has one upwind cell: no
-//                  atomics).  Interface cells that are general polyhedra go to their own
-//                  kernel (big.hip), launched on a side stream beside this one
+//                  atomics).  Meshes of rectangular hexahedra have a kernel of their own (box.hip,
+//                  two lanes per cell).  Interface cells that are general polyhedra go to
+//                  theirs (big.hip), launched on a side stream beside this one
 //   update         per cell, gather over its flux faces in ascending face id: dV from the
 //                  interface kernel or alpha_upwind*phi*dt; alpha - sum/V; round-off chopping;
 //                  cells outside the bounds are listed and compute the first sweep's corrections
@@ -439,35 +440,6 @@ __global__ void __launch_bounds__(kFindBlock) k_find_surface(const double *__res
     }
 }
 
-// The flux of face f and the velocity of cell c; with a second time level (outer iterations,
-// Crank-Nicolson) their averages, formed as they are read.
-template <bool kAvg>
-__device__ __forceinline__ double flux_at(const double *phi, const double *phi1, int32_t f) {
-    if constexpr (kAvg) return 0.5 * (phi[f] + phi1[f]);
-    else return phi[f];
-}
-__device__ __forceinline__ D3 vel_at(const double *U, const double *U1, int32_t c, size_t n) {
-    if (U1) return D3{0.5 * (U[c] + U1[c]), 0.5 * (U[n + c] + U1[n + c]), 0.5 * (U[2 * n + c] + U1[2 * n + c])};
-    return D3{U[c], U[n + c], U[2 * n + c]};
-}
-
-struct SurfArgs {
-    DevMesh m;
-    const double *alpha, *phi, *U;
-    double dt;
-    const double *dt_dom;
-    double eps, flat_tol;
-    int32_t max_rounds;
-    const int32_t *list;
-    int32_t *counters;
-    int32_t cap;
-    double *dvs;
-    int want_stats;
-    iso_trace tr;
-    const double *phi1, *U1;  // second time level, or nullptr
-    double root_tol;          // stop the isovalue search at |V_sub/V - alpha| <= root_tol (0: round-off)
-};
-
 // U_S . n_S of interface cell c (all lanes of its group).  U_S = U_P, or with us_mode 1 the
 // cell-point interpolation of the velocity to x_S: lane v takes vertex v's velocity with the
 // inverse-distance weights of the vertex values; face lane k splits its face about the vertex
@@ -553,6 +525,7 @@ __global__ void __launch_bounds__(256, kMinBlocks) k_surface(SurfArgs A) {
     // contiguous ranges per XCD would leave the XCDs with unequal work
     for (int idx = (blockIdx.x * blockDim.x + threadIdx.x) / kLanes; idx < n; idx += ngrp) {
         const int c = A.list[idx];
+        if (m.box && (m.cflags[c] & kCellBox)) continue;  // a rectangular hexahedron: k_surface_box takes it
         if constexpr (kGeneric) {
             if (m.cbig && m.cbig[c] >= 0) continue;  // a general polyhedron: k_surface_big takes it
             const int32_t L = lv < 6 ? m.cloop[6 * (size_t)c + lv] : 0;
@@ -1411,6 +1384,16 @@ __global__ void k_offset_copy(const int32_t *__restrict__ src, int32_t *__restri
     }
 }
 
+__global__ void k_stencil_copy(const int32_t *__restrict__ cell, const double *__restrict__ w, int32_t ns,
+                               int32_t *__restrict__ dcell, double *__restrict__ dw, int32_t nd, int64_t n, int32_t off) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n * nd; i += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t k = i / nd;
+        const int32_t j = (int32_t)(i - k * nd);
+        dcell[i] = cell[k * ns + (j < ns ? j : 0)] + off;
+        dw[i] = j < ns ? w[k * ns + j] : 0.0;
+    }
+}
+
 __global__ void k_slot_pairs(DevMesh m, int2 *__restrict__ pairs) {
     const int n = m.n_cells, W = m.W;
     const int64_t tot = (int64_t)n * W;
@@ -1461,8 +1444,12 @@ hipError_t launch_step(const DevMesh &m, const DevWork &w, const Params &p, cons
         const hipError_t e = launch_surface_big(bg, sb);
         if (e != hipSuccess) return e;
     }
-    if (m.all_big) {
-        // every cell is taken by the polyhedron kernel: nothing for the eight-lane one
+    if (m.box) {
+        const hipError_t e = launch_surface_box(sa, cfg, p.us_mode, s);
+        if (e != hipSuccess) return e;
+    }
+    if (m.all_big || m.box == 1) {
+        // every cell is taken by the polyhedron or the box kernel: nothing for the eight-lane one
     } else if (m.cloop && p.us_mode == 0) {
         switch (cfg.surface_waves) {
             case 1: hipLaunchKernelGGL((k_surface<1, false, true>), dim3((int)gs), dim3(bs), 0, s, sa); break;
@@ -1535,6 +1522,14 @@ hipError_t launch_offset_copy(const int32_t *src, int32_t *dst, int64_t n, int m
     if (n <= 0) return hipSuccess;
     const int g = (int)std::min<int64_t>((n + 255) / 256, 4096);
     hipLaunchKernelGGL(k_offset_copy, dim3(g), dim3(256), 0, s, src, dst, n, mode, off1, off2);
+    return hipGetLastError();
+}
+
+hipError_t launch_stencil_copy(const int32_t *cell, const double *w, int32_t ns, int32_t *dcell, double *dw, int32_t nd,
+                               int64_t n, int32_t off, hipStream_t s) {
+    if (n <= 0) return hipSuccess;
+    const int g = (int)std::min<int64_t>((n * nd + 255) / 256, 4096);
+    hipLaunchKernelGGL(k_stencil_copy, dim3(g), dim3(256), 0, s, cell, w, ns, dcell, dw, nd, n, off);
     return hipGetLastError();
 }
 

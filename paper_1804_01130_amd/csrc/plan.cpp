@@ -715,6 +715,70 @@ iso_status iso_mesh_create(int32_t n_points, const double *px, const double *py,
             if (gnp[6 * (size_t)c + k] != 0 && !((cflags[c] >> k) & 1)) all = false;
         if (all) cflags[c] |= 1 << 9;
     }
+    // rectangular hexahedra with edges exactly along the axes, when every cell is one (kCellBox)
+    bool box = !m->generic;
+    std::vector<int32_t> box_bits(box ? n_cells : 0, 0);
+    for (int32_t c = 0; c < n_cells && box; ++c) {
+        const int32_t *v = &m->cell_pts[8 * (size_t)c];
+        const V3 x0 = P(v[0]), end[3] = {P(v[1]), P(v[3]), P(v[4])};
+        double step[3][3];
+        int32_t bits = kCellBox, used = 0;
+        for (int i = 0; i < 3; ++i) {
+            const double d[3] = {end[i].x - x0.x, end[i].y - x0.y, end[i].z - x0.z};
+            int axis = -1;
+            for (int a = 0; a < 3; ++a) {
+                step[i][a] = d[a];
+                if (d[a] != 0.0) axis = axis < 0 ? a : 3;
+            }
+            if (axis < 0 || axis == 3 || !std::isfinite(d[axis]) || ((used >> axis) & 1)) { box = false; break; }
+            used |= 1 << axis;
+            bits |= axis << (13 + 3 * i);
+            if (d[axis] < 0.0) bits |= 1 << (15 + 3 * i);
+        }
+        // every vertex at its corner, coordinate for coordinate
+        static const int corner[8][3] = {{0, 0, 0}, {1, 0, 0}, {1, 1, 0}, {0, 1, 0}, {0, 0, 1}, {1, 0, 1}, {1, 1, 1}, {0, 1, 1}};
+        for (int i = 0; i < 8 && box; ++i) {
+            const V3 x = P(v[i]);
+            const double got[3] = {x.x, x.y, x.z}, base[3] = {x0.x, x0.y, x0.z};
+            for (int a = 0; a < 3; ++a) {
+                double want = base[a];
+                for (int e = 0; e < 3; ++e)
+                    if (corner[i][e] && step[e][a] != 0.0) want = e == 0 ? (a == 0 ? end[0].x : (a == 1 ? end[0].y : end[0].z))
+                                                              : e == 1 ? (a == 0 ? end[1].x : (a == 1 ? end[1].y : end[1].z))
+                                                                       : (a == 0 ? end[2].x : (a == 1 ? end[2].y : end[2].z));
+                if (got[a] != want) box = false;
+            }
+        }
+        box_bits[c] = bits;
+    }
+    std::vector<double> bext, sten_w;
+    std::vector<int32_t> sten_cell;
+    int32_t sten_n = 0;
+    if (box) {
+        int32_t most = 1;
+        for (int32_t k = 0; k < n_classes; ++k) most = std::max(most, cnt[k + 1] - cnt[k]);
+        box = most <= 8;  // (always, where no two points of the mesh coincide)
+        sten_n = most <= 4 ? 4 : 8;
+    }
+    if (box) {
+        sten_cell.resize((size_t)sten_n * n_classes);
+        sten_w.resize((size_t)sten_n * n_classes);
+        for (int32_t k = 0; k < n_classes; ++k)
+            for (int32_t j = 0; j < sten_n; ++j) {
+                const bool in = cnt[k] + j < cnt[k + 1];
+                // (a class no cell uses has no entry: any cell, weight 0)
+                sten_cell[(size_t)k * sten_n + j] = in ? st_cell[cnt[k] + j] : (cnt[k] < cnt[k + 1] ? st_cell[cnt[k]] : 0);
+                sten_w[(size_t)k * sten_n + j] = in ? st_w[cnt[k] + j] : 0.0;
+            }
+        bext.resize(3 * (size_t)n_cells);
+        for (int32_t c = 0; c < n_cells; ++c) {
+            cflags[c] |= box_bits[c];
+            const int32_t *v = &m->cell_pts[8 * (size_t)c];
+            bext[3 * (size_t)c] = norm(P(v[1]) - P(v[0]));
+            bext[3 * (size_t)c + 1] = norm(P(v[3]) - P(v[0]));
+            bext[3 * (size_t)c + 2] = norm(P(v[4]) - P(v[0]));
+        }
+    }
     std::vector<int32_t> cpt(8 * (size_t)n_cells);
     for (size_t i = 0; i < cpt.size(); ++i) cpt[i] = cls[m->cell_pts[i]];
     std::vector<double> cxyz(24 * (size_t)n_cells);
@@ -808,6 +872,8 @@ iso_status iso_mesh_create(int32_t n_points, const double *px, const double *py,
             for (int32_t c = 0; c < n_cells; ++c)
                 if (cbig[c] >= 0) cflags[c] |= 1 << 11;
     }
+    d.box = box ? 1 : 0;
+    d.sten_n = box ? sten_n : 0;
     d.n_internal = n_internal;
     d.nar_S = nar_S;
     const int32_t *pair_ptr = nullptr;
@@ -815,6 +881,8 @@ iso_status iso_mesh_create(int32_t n_points, const double *px, const double *py,
     if ((st = upload(m, cxyz, &d.cxyz)) || (st = upload(m, cpt, &d.cpt)) || (st = upload(m, m->vol, &d.vol)) ||
         (st = upload(m, slot_face, &d.slot_face)) || (st = upload(m, slot_nbr, &d.slot_nbr)) ||
         (!slot_nar.empty() && (st = upload(m, slot_nar, &d.slot_nar))) ||
+        (box && ((st = upload(m, bext, &d.bext)) || (st = upload(m, sten_cell, &d.sten_cell)) ||
+                 (st = upload(m, sten_w, &d.sten_w)))) ||
         (st = upload(m, slot_pair, &pair_ptr)) ||
         (st = upload(m, lface, &d.lface)) || (st = upload(m, cflags, &d.cflags)) || (st = upload(m, cnt, &d.st_ptr)) || (st = upload(m, st_cell, &d.st_cell)) ||
         (st = upload(m, st_w, &d.st_w)) || (st = upload(m, m->patch_alpha, &d.patch_alpha)) ||
