@@ -171,6 +171,28 @@ __device__ __forceinline__ int wave_append(int count, int32_t *counter) {
     return base + incl - count;
 }
 
+// The same for three counters (up to 2^20 elements of a wave each), their atomics in flight together.
+__device__ __forceinline__ int3 wave_append3(int3 count, int32_t *cx, int32_t *cy, int32_t *cz) {
+    const int lane = __lane_id();
+    const int top = 63 - __clzll((unsigned long long)__ballot(1));
+    const uint64_t own = (uint64_t)count.x | (uint64_t)count.y << 20 | (uint64_t)count.z << 40;
+    uint64_t incl = own;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint64_t y = __shfl_up((unsigned long long)incl, o, 64);
+        if (lane >= o) incl += y;
+    }
+    int3 b = make_int3(0, 0, 0);
+    if (lane == top && incl) {
+        b.x = atomicAdd(cx, (int)(incl & 0xFFFFF));
+        b.y = atomicAdd(cy, (int)((incl >> 20) & 0xFFFFF));
+        b.z = atomicAdd(cz, (int)(incl >> 40));
+    }
+    const uint64_t before = incl - own;
+    return make_int3(__shfl(b.x, top, 64) + (int)(before & 0xFFFFF), __shfl(b.y, top, 64) + (int)((before >> 20) & 0xFFFFF),
+                     __shfl(b.z, top, 64) + (int)(before >> 40));
+}
+
 }  // namespace
 // ------------------------------------------------------------------------------------------ sweep
 // Integral over s in [0, dt] of the submerged fraction of a triangle with signed distances

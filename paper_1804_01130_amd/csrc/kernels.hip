@@ -897,12 +897,29 @@ __device__ __forceinline__ int32_t *dlist_buf(const DevWork &w, int s, int nf) {
     return w.flist + (size_t)(1 + s % 3) * nf;
 }
 
+// The face of a slot, and a quantity of the face as seen from the slot's cell (its sign turned on
+// the neighbour's side).
+__device__ __forceinline__ int32_t face_of(int32_t v) { return v ^ (v >> 31); }
+__device__ __forceinline__ double seen_from(int32_t v, double q) {
+    return __hiloint2double(__double2hiint(q) ^ (int)(v & 0x80000000), __double2loint(q));
+}
+
 // W flux slots per cell, all loads of one kind issued together (independent gathers in flight).
-// Any block size up to 1024 (the block_cells option) is valid.  A cell left out of bounds also
-// runs phase A of the first redistribution sweep (see k_bound_sweep) here: no face is marked yet,
-// so the current dV of each of its outflow faces is the one just computed.
+// Bound by the L1: 330 line look-ups a wave, and as long again held up by look-ups of lines still on
+// their way (own face fluxes are interleaved, so three slots ask for the same lines).  Straight-line
+// code over all slots, with the exceptions mended in branches that few waves enter, took the update
+// of 256x128x128 cells from 74.4 to 68.2 us (event times), of 1024x256 from 11.9 to 10.3 and of
+// 75 k tetrahedra from 12.8 to 11.7.  Reading the slots from per-block records of their runs instead
+// of the 32-bit words, or the block's own fluxes through LDS, gave nothing more (69.6).
+// Any block size up to 1024 (the block_cells option) is valid; above eight slots 256 threads at most
+// are launched, as 1024 would leave 128 registers and the kernel needs up to 192 (64x32x32 merged
+// polyhedra: 20.8 us with 128 registers, 22 with this code spilled into them, 15.3 without a limit).
+// A cell left out of bounds also runs phase A of the first redistribution sweep (see k_bound_sweep)
+// here: no face is marked yet, so the current dV of each of its outflow faces is the one just computed.
+constexpr int update_threads(int W) { return W > 8 ? 256 : 1024; }
+
 template <int W, bool kAvg, bool kDom>
-__global__ void __launch_bounds__(1024) k_update(UpdArgs A) {
+__global__ void __launch_bounds__(update_threads(W)) k_update(UpdArgs A) {
     // no fused multiply-adds: the single-mesh and ensemble instantiations then round every
     // operation alike, and an ensemble member gets the same bits as the member stepped alone
 #pragma clang fp contract(off)
@@ -910,14 +927,8 @@ __global__ void __launch_bounds__(1024) k_update(UpdArgs A) {
     const int c = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     bool offend = false;
     int32_t v[W], o[W];
-    double ph[W], dvo[W];  // face fluxes; dV of the outflow faces (0 elsewhere)
+    double ph[W], dv[W];  // face fluxes and dV
     double x = 0.0, V = 0.0, dtc = 0.0;
-#pragma unroll
-    for (int k = 0; k < W; ++k) {
-        v[k] = kEmpty;
-        o[k] = -1;
-        ph[k] = dvo[k] = 0.0;
-    }
     if (c < n) {
         int dom = -1;  // the ensemble member, when the slot words have given it
         if (A.m.slot_nar) {
@@ -972,32 +983,62 @@ __global__ void __launch_bounds__(1024) k_update(UpdArgs A) {
         }
         const double aP = A.alpha[c];
         V = __builtin_nontemporal_load(A.m.vol + c);
-        double ao[W];
-#pragma unroll
-        for (int k = 0; k < W; ++k) {
-            const int32_t fid = v[k] >= 0 ? v[k] : ~v[k];
-            ph[k] = v[k] != kEmpty ? flux_at<kAvg>(A.phi, A.phi1, fid) : 0.0;
-            ao[k] = o[k] >= 0 ? A.alpha[o[k]] : (v[k] != kEmpty ? A.m.patch_alpha[-1 - o[k]] : 0.0);
-        }
-        const bool sP = interface_cell(aP, A.eps);
         if constexpr (kDom) dtc = dom >= 0 ? A.dt_dom[dom] : cell_dt(A.m, A.dt_dom, A.dt, c);
         else dtc = cell_dt(A.m, A.dt_dom, A.dt, c);
-        double sum = 0.0, bnd = 0.0;
+        // every slot loads (an empty one the last face, a boundary one cell 0), so that no load sits
+        // behind a branch; the cells that have such slots then put them right
+        double ao[W];
+        bool side = false;
 #pragma unroll
         for (int k = 0; k < W; ++k) {
-            if (v[k] == kEmpty) continue;
-            const int32_t fid = v[k] >= 0 ? v[k] : ~v[k];
-            const double out = v[k] >= 0 ? ph[k] : -ph[k];
-            double dv = 0.0;
-            if (out > 0.0) {
-                dv = sP ? A.dvs[fid] : aP * ph[k] * dtc;
-                dvo[k] = dv;
-            } else if (out < 0.0) {
-                dv = (o[k] >= 0 && interface_cell(ao[k], A.eps)) ? A.dvs[fid] : ao[k] * ph[k] * dtc;
+            ph[k] = flux_at<kAvg>(A.phi, A.phi1, min(face_of(v[k]), A.m.n_faces - 1));
+            ao[k] = A.alpha[max(o[k], 0)];
+            side = side || o[k] < 0;
+        }
+        if (side) {
+#pragma unroll
+            for (int k = 0; k < W; ++k) {
+                if (v[k] == kEmpty) ph[k] = 0.0;
+                else if (o[k] < 0) ao[k] = A.m.patch_alpha[-1 - o[k]];
             }
-            sum += v[k] >= 0 ? dv : -dv;
-            if (o[k] < 0) bnd += dv;  // a boundary face: the cell owns it
-            if (A.trace_dV && v[k] >= 0) A.trace_dV[fid] = dv;
+        }
+        // dV of each face: the upwind value times phi dt, or the interface kernel's where the upwind
+        // cell is an interface cell
+        uint32_t near = 0;
+#pragma unroll
+        for (int k = 0; k < W; ++k) {
+            const double out = seen_from(v[k], ph[k]);
+            const double au = out > 0.0 ? aP : ao[k];
+            if (interface_cell(au, A.eps) && (out > 0.0 || (out < 0.0 && o[k] >= 0))) near |= 1u << k;
+            dv[k] = au * ph[k] * dtc;
+        }
+        if (near) {
+#pragma unroll
+            for (int k = 0; k < W; ++k)
+                if ((near >> k) & 1) dv[k] = A.dvs[face_of(v[k])];
+        }
+        double sum = 0.0;
+#pragma unroll
+        for (int k = 0; k < W; ++k) sum += seen_from(v[k], dv[k]);
+        if (!(fabs(sum) < INFINITY)) {
+            // a face without a flux moves nothing, whatever the value upwind of it
+            sum = 0.0;
+#pragma unroll
+            for (int k = 0; k < W; ++k) {
+                if (!(ph[k] > 0.0) && !(ph[k] < 0.0)) dv[k] = 0.0;
+                sum += seen_from(v[k], dv[k]);
+            }
+        }
+        double bnd = 0.0;
+        if (A.stats) {
+#pragma unroll
+            for (int k = 0; k < W; ++k)
+                if (o[k] < 0) bnd += dv[k];  // a boundary face: the cell owns it
+        }
+        if (A.trace_dV) {
+#pragma unroll
+            for (int k = 0; k < W; ++k)
+                if (v[k] >= 0) A.trace_dV[v[k]] = dv[k];
         }
         x = aP - sum / V;
         if (A.trace_raw) A.trace_raw[c] = x;
@@ -1019,21 +1060,10 @@ __global__ void __launch_bounds__(1024) k_update(UpdArgs A) {
     const int leader = __ffsll((unsigned long long)mask) - 1;
     int base = 0;
     if (lane == leader) base = atomicAdd(&A.counters[kCntOff], __popcll(mask));
-    base = __shfl(base, leader);
-    if (offend)
-        A.olist[base + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u))] = c;
-    if (A.n_iter < 1) return;
     // phase A of sweep 0 (as in k_bound_sweep, with every face unmarked)
     const int nf = A.m.n_faces;
-    int32_t *slot = bound_slot(A.counters, 0);
-    int ndl = 0, ntl = 0;
-    int32_t fsel[W], tsel[W + 1];
-#pragma unroll
-    for (int k = 0; k <= W; ++k) tsel[k] = -1;
-#pragma unroll
-    for (int k = 0; k < W; ++k) fsel[k] = -1;
-    if (offend) {
+    uint32_t fsel = 0, tsel = 0;  // slots whose face is corrected; slots (W: the cell) to be touched
+    if (offend && A.n_iter > 0) {
         const bool over = x > 1.0 + A.tol;
         double cap[W];
         double sumcap = 0.0;
@@ -1041,13 +1071,13 @@ __global__ void __launch_bounds__(1024) k_update(UpdArgs A) {
         for (int k = 0; k < W; ++k) {
             cap[k] = 0.0;
             if (v[k] == kEmpty) continue;
-            const double outphi = v[k] >= 0 ? ph[k] : -ph[k];
+            const double outphi = seen_from(v[k], ph[k]);
             if (!(outphi > 0.0)) continue;
-            const double outv = v[k] >= 0 ? dvo[k] : -dvo[k];
+            const double outv = seen_from(v[k], dv[k]);
             cap[k] = over ? outphi * dtc - outv : outv;
             if (cap[k] > 0.0) sumcap += cap[k];
         }
-        if (atomicExch(&A.w.cmark[c], 1) == 0) tsel[W] = c;
+        if (atomicExch(&A.w.cmark[c], 1) == 0) tsel = 1u << W;
         const double need = over ? (x - 1.0) * V : -x * V;
         const double r = sumcap > 0.0 ? fmin(need / sumcap, 1.0) : 0.0;
         double bcorr = 0.0;
@@ -1055,35 +1085,37 @@ __global__ void __launch_bounds__(1024) k_update(UpdArgs A) {
         for (int k = 0; k < W; ++k) {
             if (!(sumcap > 0.0) || !(cap[k] > 0.0)) continue;
             const double d = cap[k] * r;
-            const double dd = over ? (v[k] >= 0 ? d : -d) : (v[k] >= 0 ? -d : d);
-            const int32_t f = v[k] >= 0 ? v[k] : ~v[k];
+            const double dd = seen_from(v[k], over ? d : -d);
+            const int32_t f = face_of(v[k]);
             delta_buf(A.w, 0, nf)[f] = dd;
-            A.w.dvcur[f] = dvo[k] + dd;
+            A.w.dvcur[f] = dv[k] + dd;
             A.w.fmark[f] = 1;
-            fsel[k] = f;
-            if (o[k] >= 0 && atomicExch(&A.w.cmark[o[k]], 1) == 0) tsel[k] = o[k];
+            fsel |= 1u << k;
+            if (o[k] >= 0 && atomicExch(&A.w.cmark[o[k]], 1) == 0) tsel |= 1u << k;
             if (o[k] < 0) bcorr += dd;
         }
         if (A.stats && bcorr != 0.0) A.w.sbnd[c] += bcorr;
-#pragma unroll
-        for (int k = 0; k < W; ++k) ndl += fsel[k] >= 0 ? 1 : 0;
-#pragma unroll
-        for (int k = 0; k <= W; ++k) ntl += tsel[k] >= 0 ? 1 : 0;
     }
+    base = __shfl(base, leader);
+    if (offend)
+        A.olist[base + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u))] = c;
+    if (A.n_iter < 1) return;
     // every marked face is new at sweep 0: it enters both the sweep's correction list and flist
-    int bd = wave_append(ndl, &slot[kSlotDelta]);
-    int bf = wave_append(ndl, &A.counters[kCntFaces]);
-    int bt = wave_append(ntl, &slot[kSlotTouched]);
+    int32_t *slot = bound_slot(A.counters, 0);
+    const int nd = __popc(fsel);
+    const int3 at = wave_append3(make_int3(nd, nd, __popc(tsel)), &slot[kSlotDelta], &A.counters[kCntFaces], &slot[kSlotTouched]);
+    int bd = at.x, bf = at.y, bt = at.z;
     int32_t *dlist = dlist_buf(A.w, 0, nf);
 #pragma unroll
     for (int k = 0; k < W; ++k)
-        if (fsel[k] >= 0) {
-            dlist[bd++] = fsel[k];
-            A.w.flist[bf++] = fsel[k];
+        if ((fsel >> k) & 1) {
+            dlist[bd++] = face_of(v[k]);
+            A.w.flist[bf++] = face_of(v[k]);
         }
 #pragma unroll
     for (int k = 0; k <= W; ++k)
-        if (tsel[k] >= 0) A.w.tlist[bt++] = tsel[k];
+        if ((tsel >> k) & 1) A.w.tlist[bt++] = k < W ? o[k < W ? k : 0] : c;
 }
 
 struct BoundArgs {
@@ -1177,19 +1209,13 @@ __global__ void __launch_bounds__(256) k_bound_sweep(BoundArgs A, int it) {
         }
         if (last) continue;  // uniform
         // phase A of sweep it+1 for a cell still out of bounds
-        int ndl = 0, nfl = 0, ntl = 0;
-        int32_t fsel[W], tsel[W + 1];
-        bool newf[W];
-#pragma unroll
-        for (int k = 0; k < W; ++k) { fsel[k] = -1; newf[k] = false; tsel[k] = -1; }
-        tsel[W] = -1;
+        uint32_t fsel = 0, newf = 0, tsel = 0;  // slots whose face is corrected, newly marked; touched (W: Q)
         if (again) {
-            int32_t nbr[W], fid[W];
+            int32_t fid[W];
             double ph[W];
 #pragma unroll
             for (int k = 0; k < W; ++k) {
-                nbr[k] = nb[k];
-                fid[k] = v[k] >= 0 ? v[k] : ~v[k];
+                fid[k] = face_of(v[k]);
                 ph[k] = v[k] != kEmpty ? flux_at<kAvg>(A.phi, A.phi1, fid[k]) : 0.0;
             }
             const bool over = x > 1.0 + A.tol;
@@ -1220,7 +1246,7 @@ __global__ void __launch_bounds__(256) k_bound_sweep(BoundArgs A, int it) {
                 cap[k] = over ? outphi * dtc - outv : outv;
                 if (cap[k] > 0.0) sumcap += cap[k];
             }
-            if (atomicExch(&mark_next[Q], 1) == 0) tsel[W] = Q;
+            if (atomicExch(&mark_next[Q], 1) == 0) tsel = 1u << W;
             const double need = over ? (x - 1.0) * A.m.vol[Q] : -x * A.m.vol[Q];
             const double r = sumcap > 0.0 ? fmin(need / sumcap, 1.0) : 0.0;
             double bcorr = 0.0;
@@ -1232,34 +1258,27 @@ __global__ void __launch_bounds__(256) k_bound_sweep(BoundArgs A, int it) {
                 const int32_t f = fid[k];
                 delta_next[f] = dd;
                 A.w.dvcur[f] = dvnow[k] + dd;
-                fsel[k] = f;
+                fsel |= 1u << k;
                 if (!mk[k]) {
                     A.w.fmark[f] = 1;
-                    newf[k] = true;
+                    newf |= 1u << k;
                 }
-                if (nbr[k] >= 0 && atomicExch(&mark_next[nbr[k]], 1) == 0) tsel[k] = nbr[k];
-                if (nbr[k] < 0) bcorr += dd;
+                if (nb[k] >= 0 && atomicExch(&mark_next[nb[k]], 1) == 0) tsel |= 1u << k;
+                if (nb[k] < 0) bcorr += dd;
             }
             if (A.stats && bcorr != 0.0) A.w.sbnd[Q] += bcorr;
-#pragma unroll
-            for (int k = 0; k < W; ++k) {
-                ndl += fsel[k] >= 0 ? 1 : 0;
-                nfl += newf[k] ? 1 : 0;
-            }
-#pragma unroll
-            for (int k = 0; k <= W; ++k) ntl += tsel[k] >= 0 ? 1 : 0;
         }
-        int bd = wave_append(ndl, &slot_next[kSlotDelta]);
-        int bf = wave_append(nfl, &counters[kCntFaces]);
-        int bt = wave_append(ntl, &slot_next[kSlotTouched]);
+        const int3 at = wave_append3(make_int3(__popc(fsel), __popc(newf), __popc(tsel)), &slot_next[kSlotDelta],
+                                     &counters[kCntFaces], &slot_next[kSlotTouched]);
+        int bd = at.x, bf = at.y, bt = at.z;
 #pragma unroll
         for (int k = 0; k < W; ++k) {
-            if (fsel[k] >= 0) dlist_next[bd++] = fsel[k];
-            if (newf[k]) A.w.flist[bf++] = fsel[k];
+            if ((fsel >> k) & 1) dlist_next[bd++] = face_of(v[k]);
+            if ((newf >> k) & 1) A.w.flist[bf++] = face_of(v[k]);
         }
 #pragma unroll
         for (int k = 0; k <= W; ++k)
-            if (tsel[k] >= 0) touched_next[bt++] = tsel[k];
+            if ((tsel >> k) & 1) touched_next[bt++] = k < W ? nb[k < W ? k : 0] : Q;
     }
 }
 
@@ -1361,10 +1380,11 @@ __global__ void __launch_bounds__(kStatThreads) k_stats_final(const double *part
 template <int W, bool kAvg>
 void launch_wide(const DevMesh &m, const UpdArgs &ua, const BoundArgs &ba, const LaunchCfg &cfg, hipStream_t s,
                  hipEvent_t *ev) {
-    const int gc = (m.n_cells + cfg.block_cells - 1) / cfg.block_cells;
+    const int bc = std::min(cfg.block_cells, update_threads(W));
+    const int gc = (m.n_cells + bc - 1) / bc;
     // and sweep 0's phase A; ensembles take the members' constants and time steps per cell
-    if (m.n_dom > 0) hipLaunchKernelGGL((k_update<W, kAvg, true>), dim3(gc), dim3(cfg.block_cells), 0, s, ua);
-    else hipLaunchKernelGGL((k_update<W, kAvg, false>), dim3(gc), dim3(cfg.block_cells), 0, s, ua);
+    if (m.n_dom > 0) hipLaunchKernelGGL((k_update<W, kAvg, true>), dim3(gc), dim3(bc), 0, s, ua);
+    else hipLaunchKernelGGL((k_update<W, kAvg, false>), dim3(gc), dim3(bc), 0, s, ua);
     if (ev) (void)hipEventRecord(ev[3], s);
     for (int it = 0; it < ba.n_iter; ++it)
         hipLaunchKernelGGL((k_bound_sweep<W, kAvg>), dim3(cfg.bound_blocks), dim3(256), 0, s, ba, it);
