@@ -1118,6 +1118,10 @@ __global__ void __launch_bounds__(update_threads(W)) k_update(UpdArgs A) {
         if ((tsel >> k) & 1) A.w.tlist[bt++] = k < W ? o[k < W ? k : 0] : c;
 }
 
+// (see k_bound_group)
+constexpr int kBoundGroupCells = 1 << 17;
+constexpr int bound_threads(int W) { return W > 8 ? 512 : 1024; }
+
 struct BoundArgs {
     DevMesh m;
     const double *alpha, *phi, *dvs;
@@ -1139,23 +1143,23 @@ struct BoundArgs {
 // after phase B of sweep s runs phase A of sweep s+1 at once: one kernel per sweep (phase A of
 // sweep 0 runs inside the update).  Touched lists and marks alternate between two banks, counter
 // slots rotate over four.  List order never affects a result.
+// Where a sweep finds and leaves its counts: the counter slots in memory, or a work-group's own.
+struct BoundCounts {
+    int stale, touched, faces;  // sweep it-1's corrections; cells touched in sweep it; faces marked so far
+    int32_t *delta_next, *touched_next, *faces_next;
+};
+
+// Sweep `it`, over the cells b0 + threadIdx.x, and so on every `stride`.
 template <int W, bool kAvg>
-__global__ void __launch_bounds__(256) k_bound_sweep(BoundArgs A, int it) {
+__device__ __forceinline__ void bound_sweep(const BoundArgs &A, int it, int b0, int stride, const BoundCounts &C) {
     const int n = A.m.n_cells, nf = A.m.n_faces;
-    int32_t *counters = A.w.counters;
-    const int stride = gridDim.x * blockDim.x;
-    const int t0 = blockIdx.x * blockDim.x + threadIdx.x;
+    const int t0 = b0 + threadIdx.x;
     const bool last = it == A.n_iter - 1;
-    if (it >= 1) {  // sweep it-1's corrections were read by the previous kernel: clear them
-        const int n_stale = bound_slot(counters, it - 1)[kSlotDelta];
+    if (it >= 1) {  // sweep it-1's corrections were read before this sweep: clear them
         double *stale = delta_buf(A.w, it - 1, nf);
         const int32_t *slist = dlist_buf(A.w, it - 1, nf);
-        for (int i = t0; i < n_stale; i += stride) stale[slist[i]] = 0.0;
+        for (int i = t0; i < C.stale; i += stride) stale[slist[i]] = 0.0;
     }
-    // nothing reads sweep it-2's counters any more (its slot returns for sweep it+2)
-    if (it >= 2 && blockIdx.x == 0 && threadIdx.x < 2) bound_slot(counters, it - 2)[threadIdx.x] = 0;
-    const int32_t *slot = bound_slot(counters, it);
-    int32_t *slot_next = bound_slot(counters, it + 1);
     const double *delta = delta_buf(A.w, it, nf);
     double *delta_next = delta_buf(A.w, it + 1, nf);
     int32_t *dlist_next = dlist_buf(A.w, it + 1, nf);
@@ -1163,15 +1167,14 @@ __global__ void __launch_bounds__(256) k_bound_sweep(BoundArgs A, int it) {
     int32_t *touched_next = A.w.tlist + (size_t)((it + 1) & 1) * n;
     int32_t *mark = A.w.cmark + (size_t)(it & 1) * n;
     int32_t *mark_next = A.w.cmark + (size_t)((it + 1) & 1) * n;
-    const int nT = slot[kSlotTouched];
+    const int nT = C.touched;
     if (last) {
         // no phase A in the last sweep reads the face marks, and the list of marked faces is
-        // complete: clear them here, over the whole grid, rather than in the end kernel
-        const int nF = counters[kCntFaces];
-        for (int i = t0; i < nF; i += stride) A.w.fmark[A.w.flist[i]] = 0;
+        // complete: clear them here, over the whole grid, rather than at the end
+        for (int i = t0; i < C.faces; i += stride) A.w.fmark[A.w.flist[i]] = 0;
     }
-    const int nloop = (nT + 255) & ~255;  // whole work-groups iterate together
-    for (int i0 = blockIdx.x * blockDim.x; i0 < nloop; i0 += stride) {
+    const int nloop = (nT + (int)blockDim.x - 1) / (int)blockDim.x * (int)blockDim.x;  // whole work-groups iterate together
+    for (int i0 = b0; i0 < nloop; i0 += stride) {
         const int i = i0 + threadIdx.x;
         bool again = false;
         int32_t Q = 0;
@@ -1268,8 +1271,8 @@ __global__ void __launch_bounds__(256) k_bound_sweep(BoundArgs A, int it) {
             }
             if (A.stats && bcorr != 0.0) A.w.sbnd[Q] += bcorr;
         }
-        const int3 at = wave_append3(make_int3(__popc(fsel), __popc(newf), __popc(tsel)), &slot_next[kSlotDelta],
-                                     &counters[kCntFaces], &slot_next[kSlotTouched]);
+        const int3 at = wave_append3(make_int3(__popc(fsel), __popc(newf), __popc(tsel)), C.delta_next, C.faces_next,
+                                     C.touched_next);
         int bd = at.x, bf = at.y, bt = at.z;
 #pragma unroll
         for (int k = 0; k < W; ++k) {
@@ -1282,10 +1285,22 @@ __global__ void __launch_bounds__(256) k_bound_sweep(BoundArgs A, int it) {
     }
 }
 
-// End of the step (one work-group): chop the listed cells when no sweep ran, clear the correction
-// buffer of the last sweep (the last sweep itself has cleared the face marks), keep this step's
-// counters for the statistics and zero them for the next step.
-__global__ void __launch_bounds__(1024) k_bound_end(BoundArgs A) {
+template <int W, bool kAvg>
+__global__ void __launch_bounds__(256) k_bound_sweep(BoundArgs A, int it) {
+    int32_t *counters = A.w.counters;
+    // nothing reads sweep it-2's counters any more (its slot returns for sweep it+2)
+    if (it >= 2 && blockIdx.x == 0 && threadIdx.x < 2) bound_slot(counters, it - 2)[threadIdx.x] = 0;
+    int32_t *next = bound_slot(counters, it + 1);
+    bound_sweep<W, kAvg>(A, it, blockIdx.x * blockDim.x, gridDim.x * blockDim.x,
+                         {it >= 1 ? bound_slot(counters, it - 1)[kSlotDelta] : 0, bound_slot(counters, it)[kSlotTouched],
+                          it == A.n_iter - 1 ? counters[kCntFaces] : 0, &next[kSlotDelta], &next[kSlotTouched],
+                          &counters[kCntFaces]});
+}
+
+// End of the step, by one work-group: chop the listed cells when no sweep ran, clear the correction
+// buffer of the last sweep (`nd` corrections; the last sweep itself has cleared the face marks), keep
+// this step's counters for the statistics and zero them for the next step.
+__device__ __forceinline__ void bound_end(const BoundArgs &A, int nd) {
     const int tid = threadIdx.x, nt = blockDim.x;
     const int nf = A.m.n_faces;
     int32_t *counters = A.w.counters;
@@ -1299,22 +1314,55 @@ __global__ void __launch_bounds__(1024) k_bound_end(BoundArgs A) {
                 if (A.stats) A.w.sclip[P] += (y - x) * A.m.vol[P];
             }
         }
-    } else {
-        const int it = A.n_iter - 1;
-        const int nd = bound_slot(counters, it)[kSlotDelta];
-        const int32_t *dl = dlist_buf(A.w, it, nf);
-        double *delta = delta_buf(A.w, it, nf);
-        for (int i = tid; i < nd; i += nt) delta[dl[i]] = 0.0;
-    }
-    if (A.n_iter == 0) {  // (with sweeps, the last one has cleared the face marks)
-        const int nF = counters[kCntFaces];
+        const int nF = counters[kCntFaces];  // (with sweeps, the last one has cleared the face marks)
         for (int i = tid; i < nF; i += nt) A.w.fmark[A.w.flist[i]] = 0;
+    } else {
+        const int32_t *dl = dlist_buf(A.w, A.n_iter - 1, nf);
+        double *delta = delta_buf(A.w, A.n_iter - 1, nf);
+        for (int i = tid; i < nd; i += nt) delta[dl[i]] = 0.0;
     }
     __syncthreads();
     if (tid < 8) counters[8 + tid] = tid == kCntActive0 ? counters[kCntOff] : counters[tid];
     __syncthreads();
     if (tid < 8) counters[tid] = 0;
     if (tid >= kCntBound && tid < kCntBound + 8) counters[tid] = 0;
+}
+
+__global__ void __launch_bounds__(1024) k_bound_end(BoundArgs A) {
+    bound_end(A, A.n_iter > 0 ? bound_slot(A.w.counters, A.n_iter - 1)[kSlotDelta] : 0);
+}
+
+// The sweeps from `first` on and the end of the step in one work-group, its counts in LDS.  What a
+// sweep costs is its launch and one chain of dependent loads, as long as its list is no longer than
+// the work-group; a long list wants the whole chip, and the first one is the longest.  So up to
+// kBoundGroupCells every sweep runs here, above it the first sweep runs on the grid, and all sweeps of
+// an ensemble, whose lists are those of its members together.
+// Whole steps in us, all sweeps on the grid / first on the grid / none:
+//   calm slab 384x96 34.8 / - / 30.2, 1024x256 40.7 / 38.3 / 35.6, box 151x75x85 68.1 / 63.8 / 61.1
+//   violent box (cells out of bounds) 64x32x32 (100) 46.0 / 43.8 / 41.9, 96x48x48 (300)
+//   58.7 / 55.9 / 60.3, 128x64x64 (500) 74.8 / 72.1 / 85.3, 256x128x128 (1200) 169.4 / 169.5 / -;
+//   calm 250x128x128 124.5 / 121.0 / 120.4; 5 steps of an ensemble of 64 tanks 856 / 895 / -
+// With a second sweep on the grid, 66.8 on 151x75x85 and 73.6 on 128x64x64.
+template <int W, bool kAvg>
+__global__ void __launch_bounds__(bound_threads(W)) k_bound_group(BoundArgs A, int first) {
+    __shared__ int32_t cnt[2][4], faces;
+    int32_t *counters = A.w.counters;
+    const int tid = threadIdx.x;
+    if (tid < 2) cnt[first & 1][tid] = bound_slot(counters, first)[tid];
+    if (tid == 2) faces = counters[kCntFaces];
+    int stale = first > 0 ? bound_slot(counters, first - 1)[kSlotDelta] : 0;
+    for (int it = first; it < A.n_iter; ++it) {
+        int32_t *now = cnt[it & 1], *next = cnt[(it + 1) & 1];
+        if (tid < 2) next[tid] = 0;
+        __syncthreads();
+        const int nT = now[kSlotTouched], nd = now[kSlotDelta], nF = faces;
+        __syncthreads();
+        bound_sweep<W, kAvg>(A, it, 0, blockDim.x, {stale, nT, nF, &next[kSlotDelta], &next[kSlotTouched], &faces});
+        stale = nd;
+        __syncthreads();
+    }
+    if (tid == 0) counters[kCntFaces] = faces;
+    bound_end(A, stale);
 }
 
 // Step statistics in two passes with a fixed order of summation (results do not depend on timing):
@@ -1386,8 +1434,14 @@ void launch_wide(const DevMesh &m, const UpdArgs &ua, const BoundArgs &ba, const
     if (m.n_dom > 0) hipLaunchKernelGGL((k_update<W, kAvg, true>), dim3(gc), dim3(bc), 0, s, ua);
     else hipLaunchKernelGGL((k_update<W, kAvg, false>), dim3(gc), dim3(bc), 0, s, ua);
     if (ev) (void)hipEventRecord(ev[3], s);
-    for (int it = 0; it < ba.n_iter; ++it)
+    // sweeps over the whole grid
+    const int grid = std::min(ba.n_iter, m.n_cells <= kBoundGroupCells ? 0 : m.n_dom > 0 ? ba.n_iter : 1);
+    for (int it = 0; it < grid; ++it)
         hipLaunchKernelGGL((k_bound_sweep<W, kAvg>), dim3(cfg.bound_blocks), dim3(256), 0, s, ba, it);
+    if (grid < ba.n_iter) {
+        hipLaunchKernelGGL((k_bound_group<W, kAvg>), dim3(1), dim3(bound_threads(W)), 0, s, ba, grid);
+        return;
+    }
     hipLaunchKernelGGL(k_bound_end, dim3(1), dim3(1024), 0, s, ba);
 }
 

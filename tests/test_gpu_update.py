@@ -58,3 +58,34 @@ def test_block_sizes_of_many_sided_cells(block_cells):
     ref = gpu_trajectory(plan, w, 3)
     gm, plan = gpu_plan(w.mesh, block_cells=block_cells)
     assert np.array_equal(gpu_trajectory(plan, w, 3), ref)
+
+
+@pytest.mark.parametrize("n_bound_iter", [0, 1, 2, 3, 7])
+@pytest.mark.parametrize("size", [(48, 32, 32), (72, 48, 48)])
+def test_sweeps_in_one_work_group_and_on_the_grid(size, n_bound_iter):
+    """A mesh whose sweeps run in one work-group (49152 cells) or after the first (165888), alone and as a
+    member of an ensemble, whose sweeps run on the grid: the same bits, from fields that leave cells out
+    of bounds in every sweep, over more touched cells than the work-group has threads."""
+    import torch
+    from paper_1804_01130_amd import Batch, Mesh, Plan, default_options
+    w = W.violent_3d(nx=size[0], ny=size[1], nz=size[2], steps=3)
+    m = Mesh.from_arrays(w.mesh)
+    opts = default_options(n_bound_iter=n_bound_iter)
+    rng = np.random.default_rng(5)
+    a0 = [w.alpha0, rng.uniform(0.0, 1.0, w.mesh.n_cells), np.where(rng.random(w.mesh.n_cells) < 0.02, rng.random(w.mesh.n_cells), w.alpha0)]
+    phi, U = w.phi_U(0)
+    say(f"[gpu] sweeps: {size} n_bound_iter={n_bound_iter}")
+    plan, alone, active = Plan(m, opts), [], []
+    for a in a0:
+        a, b = to_dev(a), torch.empty(m.n_cells, dtype=torch.float64, device=dev())
+        for _ in range(3):
+            _, st = plan.step(a, to_dev(phi), to_dev(U), w.dt, out=b, stats=True)
+            a, b = b, a
+        active.append(st["n_bound_active"])
+        alone.append(a)
+    assert max(active) > 300
+    batch = Batch([m] * 3, opts)
+    x = to_dev(batch.concat_cells(a0))
+    batch.advect(x, torch.cat([to_dev(phi)] * 3), to_dev(batch.concat_U([U] * 3)), np.full(3, w.dt), 3)
+    torch.cuda.synchronize()
+    assert torch.equal(x, torch.cat(alone))
