@@ -10,14 +10,13 @@
 //   unsweep    two per sweep, in reverse: the bounding step (end of Section 3.2) transposed
 //   faces      per cell, a gather over its flux faces: transposes of the flux-form update and of
 //              the bulk fluxes alpha_upwind phi dt; phi's adjoint through dV = phi * (dV/phi); and
-//              the interface cells' directions (their isovalue, and each vertex value a cut edge
-//              touches)
-//   surface    eight lanes per (interface cell, direction): rates of the sub-volume and of the
-//              swept face integrals (Eqs. tv .. intaplus) by forward-mode dual numbers through
-//              the isoface
-//   points     per point class, and cells, per cell: the isovalue moving with the volume
-//              constraint (implicit function) combines the rates, and the transpose of the
-//              vertex interpolation gathers them to the stencil cells in a fixed order
+//              the list of interface cells
+//   surface    eight lanes per interface cell: the isoface, the sub-volume and the swept face
+//              integrals (Eqs. tv .. intaplus) run backwards to the vertex values, the isovalue moving
+//              with the volume constraint (implicit function); general polyhedra by forward-mode dual
+//              numbers, sixteen lanes per (polyhedron, point value)
+//   points     per point class, and cells, per cell: the transpose of the vertex interpolation
+//              gathers the vertex adjoints to the stencil cells in a fixed order
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -33,7 +32,6 @@ struct Dl {
 };
 __device__ __forceinline__ Dl operator+(Dl a, Dl b) { return {a.v + b.v, a.d + b.d}; }
 __device__ __forceinline__ Dl operator-(Dl a, Dl b) { return {a.v - b.v, a.d - b.d}; }
-__device__ __forceinline__ Dl operator-(Dl a) { return {-a.v, -a.d}; }
 __device__ __forceinline__ Dl operator*(Dl a, Dl b) { return {a.v * b.v, a.d * b.v + a.v * b.d}; }
 __device__ __forceinline__ Dl operator*(double s, Dl a) { return {s * a.v, s * a.d}; }
 __device__ __forceinline__ Dl operator/(Dl a, Dl b) {
@@ -48,7 +46,6 @@ __device__ __forceinline__ Dl dsqrt(Dl a) {
     const double r = sqrt(a.v);
     return {r, r > 0.0 ? 0.5 * a.d / r : 0.0};
 }
-__device__ __forceinline__ Dl dsel(bool c, Dl a, Dl b) { return {c ? a.v : b.v, c ? a.d : b.d}; }
 __device__ __forceinline__ Dl dc(double x) { return {x, 0.0}; }
 
 struct DV3 {
@@ -64,155 +61,6 @@ __device__ __forceinline__ DV3 dcross(DV3 a, DV3 b) {
     return {a.y * b.z - a.z * b.y, a.z * b.x - a.x * b.z, a.x * b.y - a.y * b.x};
 }
 __device__ __forceinline__ Dl dnorm(DV3 a) { return dsqrt(ddot(a, a)); }
-__device__ __forceinline__ DV3 dsel3(bool c, DV3 a, DV3 b) { return {dsel(c, a.x, b.x), dsel(c, a.y, b.y), dsel(c, a.z, b.z)}; }
-__device__ __forceinline__ Dl dgrp_sum(Dl a) { return {grp_sum(a.v), grp_sum(a.d)}; }
-__device__ __forceinline__ DV3 dgrp_sum3(DV3 a) { return {dgrp_sum(a.x), dgrp_sum(a.y), dgrp_sum(a.z)}; }
-
-// A lane's face with dual vertex values (geometry is fixed).
-struct DFace {
-    D3 q[4];
-    Dl aq[4];
-    Dl inv[4];
-    int fwd;
-    bool planar, active;
-};
-
-__device__ __forceinline__ DV3 dface_cut(const DFace &f, int i, Dl iso, bool wet_i) {
-    const int j = (i + 1) & 3;
-    const bool fwd = (f.fwd >> i) & 1;
-    const D3 xw = sel3(wet_i, f.q[i], f.q[j]), xd = sel3(wet_i, f.q[j], f.q[i]);
-    const Dl aw = dsel(wet_i, f.aq[i], f.aq[j]);
-    const Dl lam = (wet_i == fwd) ? (iso - aw) * f.inv[i] : (aw - iso) * f.inv[i];
-    return dv(xw) + lam * dv(xd - xw);
-}
-
-struct DPart {
-    Dl v6;
-    DV3 cseg, oacc;
-    Dl oL;
-    DV3 osum;
-    double nseg;
-};
-
-// The face's share of six times the sub-volume and of the isoface sums (the same construction as
-// the forward kernel, in dual numbers; wet iff a > iso).
-__device__ __forceinline__ DPart dface_part(const DFace &f, Dl iso) {
-    const DV3 Z = dv(D3{0, 0, 0});
-    DPart r{dc(0.0), Z, Z, dc(0.0), Z, 0.0};
-    bool w[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) w[i] = f.active && f.aq[i].v > iso.v;
-    DV3 cut[4];
-    bool cuts[4], exits[4], entries[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int j = (i + 1) & 3;
-        cut[i] = dface_cut(f, i, iso, w[i]);
-        cuts[i] = w[i] != w[j];
-        exits[i] = w[i] && !w[j];
-        entries[i] = !w[i] && w[j];
-    }
-    DV3 last = Z;
-    int cnt = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        last = dsel3(w[i], dv(f.q[i]), last);
-        last = dsel3(cuts[i], cut[i], last);
-        cnt += (w[i] ? 1 : 0) + (cuts[i] ? 1 : 0);
-    }
-    DV3 C = Z, prev = last;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        C = dsel3(w[i], C + dcross(prev, dv(f.q[i])), C);
-        prev = dsel3(w[i], dv(f.q[i]), prev);
-        C = dsel3(cuts[i], C + dcross(prev, cut[i]), C);
-        prev = dsel3(cuts[i], cut[i], prev);
-    }
-    if (cnt >= 3) {
-        DV3 ap = dv(f.q[0]);
-        if (!f.planar) {
-            DV3 pacc = Z, psum = Z, pv = last;
-            Dl pl = dc(0.0);
-            auto step = [&](bool on, DV3 x) {
-                const Dl l = dnorm(x - pv);
-                pacc = dsel3(on, pacc + (0.5 * l) * (x + pv), pacc);
-                pl = dsel(on, pl + l, pl);
-                psum = dsel3(on, psum + x, psum);
-                pv = dsel3(on, x, pv);
-            };
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                step(w[i], dv(f.q[i]));
-                step(cuts[i], cut[i]);
-            }
-            ap = pl.v > 0.0 ? dinv(pl) * pacc : (1.0 / cnt) * psum;
-        }
-        r.v6 = ddot(ap, C);
-    }
-    DV3 lastexit = Z;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) lastexit = dsel3(exits[i], cut[i], lastexit);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const DV3 s0 = cut[i], s1 = lastexit;
-        if (entries[i]) {
-            const Dl l = dnorm(s1 - s0);
-            r.cseg = r.cseg + dcross(s0, s1);
-            r.oacc = r.oacc + (0.5 * l) * (s0 + s1);
-            r.oL = r.oL + l;
-            r.osum = r.osum + s0;
-            r.nseg += 1.0;
-        }
-        lastexit = dsel3(exits[i], cut[i], lastexit);
-    }
-    return r;
-}
-
-// Six times the sub-volume (all lanes of the group), and the isoface apex and area vector (x2).
-__device__ __forceinline__ Dl dcell_vsub6(const DFace &f, Dl iso, DV3 *o_out, DV3 *cseg_out) {
-    const DPart p = dface_part(f, iso);
-    const Dl v6 = dgrp_sum(p.v6);
-    const DV3 cseg = dgrp_sum3(p.cseg), oacc = dgrp_sum3(p.oacc), osum = dgrp_sum3(p.osum);
-    const Dl oL = dgrp_sum(p.oL);
-    const double nseg = grp_sum(p.nseg);
-    const DV3 Z = dv(D3{0, 0, 0});
-    const DV3 o = oL.v > 0.0 ? dinv(oL) * oacc : (nseg > 0.0 ? (1.0 / nseg) * osum : Z);
-    if (o_out) *o_out = o;
-    if (cseg_out) *cseg_out = cseg;
-    return v6 + ddot(o, cseg);
-}
-
-__device__ __forceinline__ void dface_centre_part(const DFace &f, Dl iso, DV3 o, DV3 n, DV3 &acc, Dl &ws) {
-    const DV3 Z = dv(D3{0, 0, 0});
-    acc = Z;
-    ws = dc(0.0);
-    bool w[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) w[i] = f.active && f.aq[i].v > iso.v;
-    DV3 cut[4];
-    bool exits[4], entries[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int j = (i + 1) & 3;
-        cut[i] = dface_cut(f, i, iso, w[i]);
-        exits[i] = w[i] && !w[j];
-        entries[i] = !w[i] && w[j];
-    }
-    DV3 lastexit = Z;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) lastexit = dsel3(exits[i], cut[i], lastexit);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const DV3 s0 = cut[i], s1 = lastexit;
-        if (entries[i]) {
-            const Dl wt = ddot(dcross(s0 - o, s1 - o), n);
-            acc = acc + wt * (o + s0 + s1);
-            ws = ws + wt;
-        }
-        lastexit = dsel3(exits[i], cut[i], lastexit);
-    }
-}
-
 // Swept integral of a triangle (the forward kernel's construction in dual numbers): the wet
 // fraction at time s is the area distribution of the distances at un*s; breakpoints clamped to
 // the window; each piece integrated exactly (Simpson) on the branch of its midpoint.
@@ -701,181 +549,420 @@ __global__ void __launch_bounds__(256) k_adj_faces(AdjArgs A) {
     const int n = A.m.n_cells;
     const int c = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;  // contiguous ranges per XCD
     if (c < n) adj_faces_cell<W>(A, c);
-    // the interface-cell directions k_adj_surface differentiates along: the isovalue, and each vertex
-    // value that moves a cut point (a vertex no cut edge touches moves nothing: its rates are zero)
-    uint32_t need = 0;
     int nbig = 0;  // a general polyhedron: every point value and the isovalue (kBigIsoDir)
-    const bool big = c < n && A.m.cbig && A.m.cbig[c] >= 0;
-    if (big && A.kind[c] == 1) {
+    const bool cut = c < n && A.kind[c] == 1, big = cut && A.m.cbig && A.m.cbig[c] >= 0;
+    if (big) {
         const int bi = A.m.cbig[c];
         nbig = A.m.bv_ptr[bi + 1] - A.m.bv_ptr[bi] + 1;
-    } else if (c < n && A.kind[c] == 1) {
-        const double iso = A.iso[c];
-        uint32_t wet = 0;
-#pragma unroll
-        for (int v = 0; v < 8; ++v) wet |= (A.vert_alpha[8 * (size_t)c + v] > iso ? 1u : 0u) << v;
-        if (A.m.cloop) {  // the edges of the cell's own face loops (a triangle's repeated point: none)
-            for (int k = 0; k < 6; ++k) {
-                const int32_t L = A.m.cloop[6 * (size_t)c + k];
-                if (!((L >> 12) & 1)) continue;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int p = (L >> (3 * i)) & 7, q = (L >> (3 * ((i + 1) & 3))) & 7;
-                    if (((wet >> p) ^ (wet >> q)) & 1u) need |= (1u << p) | (1u << q);
-                }
-            }
-        } else {
-#pragma unroll
-            for (int t = 0; t < 12; ++t)
-                if (((wet >> kEdge[t][0]) ^ (wet >> kEdge[t][1])) & 1u)
-                    need |= (1u << kEdge[t][0]) | (1u << kEdge[t][1]);
-        }
-        double *gb = A.w.gbuf + (size_t)kAdjG * c;
-#pragma unroll
-        for (int v = 0; v < 8; ++v)
-            if (!((need >> v) & 1u)) {
-                gb[v] = 0.0;
-                gb[9 + v] = 0.0;
-            }
-        need |= 1u << 8;
     }
-    int b = block_append(__popc(need), &A.w.counters[kAdjDirs]);
-    for (int d = 0; d < 9; ++d)
-        if ((need >> d) & 1u) A.w.dlist[b++] = ((int64_t)c << 4) | d;
+    const int b = block_append(cut && !big ? 1 : 0, &A.w.counters[kAdjCells]);
+    if (cut && !big) A.w.clist[b] = c;
     if (!A.m.cbig) return;  // uniform: no polyhedra in this mesh
     int bb = block_append(nbig, &A.w.counters[kAdjDirsBig]);
     for (int d = 0; d + 1 < nbig; ++d) A.w.dlist_big[bb++] = ((int64_t)c << 6) | d;
     if (nbig) A.w.dlist_big[bb] = ((int64_t)c << 6) | kBigIsoDir;
 }
 
-// interface cells: rates of the sub-volume and the swept integrals along each listed direction
-__global__ void __launch_bounds__(256, 2) k_adj_surface(AdjArgs A) {
+// ------------------------------------------------------------------------ interface cells (8 lanes)
+// Rates of a triangle's swept integral with its vertices' distances and the normal speed: the integral
+// over the window of the rates of G(un s), G the triangle's area distribution, piece by piece between
+// its breakpoints (their integrands are quadratic, so the moments below are exact), and at a breakpoint
+// where G jumps (three equal distances) the jump times the breakpoint's rate.
+struct TriRates {
+    double p0, p1, p2, pu;
+};
+__device__ __forceinline__ TriRates tri_rates(double d0, double d1, double d2, double un, double dt) {
+    double e1 = d0, e2 = d1, e3 = d2;
+    int i1 = 0, i2 = 1, i3 = 2;
+    auto order = [](double &x, double &y, int &ix, int &iy) {
+        const bool swap = y < x;
+        const double t = swap ? y : x, u = swap ? x : y;
+        const int it = swap ? iy : ix, iu = swap ? ix : iy;
+        x = t;
+        y = u;
+        ix = it;
+        iy = iu;
+    };
+    order(e1, e2, i1, i2);
+    order(e2, e3, i2, i3);
+    order(e1, e2, i1, i2);
+    const double r31 = e3 > e1 ? 1.0 / (e3 - e1) : 0.0;
+    const double r21 = e2 > e1 ? 1.0 / (e2 - e1) : 0.0;
+    const double r32 = e3 > e2 ? 1.0 / (e3 - e2) : 0.0;
+    double q1 = 0.0, q2 = 0.0, q3 = 0.0, qu = 0.0;
+    const double inv = un != 0.0 ? 1.0 / un : 0.0;
+    const bool up = un > 0.0;
+    // breakpoints in the order they are met, clamped to the window (a speed of zero meets none)
+    const double sa = up ? e1 * inv : e3 * inv, sb = e2 * inv, sc = up ? e3 * inv : e1 * inv;
+    auto clamp = [&](double x) { return un == 0.0 || x <= 0.0 ? 0.0 : (x >= dt ? dt : x); };
+    const double bk[4] = {clamp(sa), clamp(sb), clamp(sc), dt};
+    double jump[3] = {0.0, 0.0, 0.0};
+    double a0 = 0.0;
+    int prev = -1;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const double a1 = bk[k];
+        if (a1 > a0) {
+            const double z = un * (0.5 * (a0 + a1));
+            const bool rising = z < e2;  // on the branch of the smallest distance, else of the largest
+            double fa = z < e1 ? 0.0 : 1.0, fb = fa;
+            if (z >= e1 && z < e3) {
+                const double z0 = un * a0, h = a1 - a0;
+                const double u0 = rising ? z0 - e1 : e3 - z0, u1 = u0 + (rising ? un : -un) * h;
+                const double rB = rising ? r21 : r32, kk = r31 * rB;
+                const double m1 = h * (u0 + u1), m2 = (1.0 / 3.0) * h * (u0 * u0 + u0 * u1 + u1 * u1);
+                const double ms = (1.0 / 3.0) * h * (u0 * (a0 + a0 + a1) + u1 * (a0 + a1 + a1));
+                const double self = kk * (m2 * (r31 + rB) - m1), other = -kk * r31 * m2;
+                q1 += rising ? self : other;
+                q3 += rising ? other : self;
+                q2 -= kk * rB * m2;
+                qu += kk * ms;
+                const double g0 = (u0 * r31) * (u0 * rB), g1 = (u1 * r31) * (u1 * rB);
+                fa = rising ? g0 : 1.0 - g0;
+                fb = rising ? g1 : 1.0 - g1;
+            }
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                if (j < k && j == prev) jump[j] -= fa;
+            if (k < 3) jump[k < 3 ? k : 0] += fb;
+            prev = k;
+            a0 = a1;
+        }
+    }
+    // (a breakpoint clamped to the window's end does not move)
+    const double ja = sa < dt ? jump[0] * inv : 0.0, jb = sb < dt ? jump[1] * inv : 0.0, jc = sc < dt ? jump[2] * inv : 0.0;
+    q1 += up ? ja : jc;
+    q2 += jb;
+    q3 += up ? jc : ja;
+    qu -= ja * sa + jb * sb + jc * sc;
+    auto back = [](bool first, double a, bool second, double b, double c) { return first ? a : (second ? b : c); };
+    return {back(i1 == 0, q1, i2 == 0, q2, q3), back(i1 == 1, q1, i2 == 1, q2, q3), back(i1 == 2, q1, i2 == 2, q2, q3), qu};
+}
+
+// One edge of the isoface: the face's wet loop enters at cut s0 (between wet vertex qn and a dry one)
+// and left at cut s1 (from wet vertex qx).
+struct IsoEdge {
+    D3 s0, s1, t0, t1, qn, qx;      // cuts; wet to dry along their edges; wet ends
+    double lam0, lam1, g0, g1;      // cut = wet end + lam t; rate of lam with the isovalue
+    int n, dn, x, dx;               // the cell's vertices: wet and dry end of the entry, of the exit
+    bool on;
+};
+
+// adjoints of the edge's cuts from those of o's sums, (s0 + s1) |s1 - s0| / 2 and |s1 - s0|, and of
+// the area vector s0 x s1
+__device__ __forceinline__ void iso_edge_back(const IsoEdge &S, D3 oab, double olb, D3 csb, D3 &s0b, D3 &s1b) {
+    const D3 d = S.s1 - S.s0;
+    const double l = norm3(d);
+    const double lb = 0.5 * dot(oab, S.s0 + S.s1) + olb, q = l > 0.0 ? lb / l : 0.0;
+    const D3 half = 0.5 * l * oab;
+    s0b = s0b + half - q * d + cross(S.s1, csb);
+    s1b = s1b + half + q * d + cross(csb, S.s0);
+}
+
+// Interface cells: adjoints of the vertex values and of alpha through the cell's isoface, by reverse
+// accumulation; one group of eight lanes per cell, one lane per face, in the forward kernel's
+// construction.  Two functions of the vertex values and the isovalue are differentiated: six times the
+// sub-volume (G) and the faces' adjoint-weighted swept integrals (C), whose rate with the normal, the
+// centre and the apex runs back over the same isoface edges.
+// Bound by latency: one chain of some 2500 FP64 instructions per cell.  A forward-mode pass per
+// direction (up to nine a cell, eight lanes each) took 72.9 us on 128x64x64 cells and 13.3 on a slab of
+// 256x128; this takes 20.7 and 10.7.  It holds 376 registers, one wave per SIMD; with two (256
+// registers, the rest spilled) 25.8 and 12.9.
+__global__ void __launch_bounds__(64) k_adj_surface(AdjArgs A) {
     const DevMesh &m = A.m;
     const int lv = threadIdx.x & (kLanes - 1);
     const int ngrp = (gridDim.x * blockDim.x) / kLanes;
-    const int npair = A.w.counters[kAdjDirs];
+    const int ncell = A.w.counters[kAdjCells];
+    const D3 Z{0, 0, 0};
     int fv[4];
-    int fwd = lane_face_loop(lv, fv);
+    lane_face_loop(lv, fv);
     bool face_on = lv < 6;
-    for (int g = (blockIdx.x * blockDim.x + threadIdx.x) / kLanes; g < npair; g += ngrp) {
-        const int64_t pr = A.w.dlist[g];
-        const int c = (int)(pr >> 4);
-        const int dir = (int)(pr & 15);  // 0..7: vertex value dir, 8: the isovalue
+    for (int g = (blockIdx.x * blockDim.x + threadIdx.x) / kLanes; g < ncell; g += ngrp) {
+        const int c = A.w.clist[g];
         if (m.cloop) {  // cells other than hexahedra: the cell's own face loops, as in the step
             const int32_t L = lv < 6 ? m.cloop[6 * (size_t)c + lv] : 0;
 #pragma unroll
             for (int i = 0; i < 4; ++i) fv[i] = (L >> (3 * i)) & 7;
-            fwd = (L >> 16) & 15;
             face_on = (L >> 12) & 1;
         }
         const double aP = A.alpha[c];
         const double V6 = 6.0 * m.vol[c];
         const double dtc = cell_dt(m, A.dt_dom, A.dt, c);
+        const double iso = A.iso[c];
+        const D3 U{A.U[c], A.U[m.n_cells + c], A.U[2 * (size_t)m.n_cells + c]};
+        const bool planar = (m.cflags[c] >> min(lv, 5)) & 1;
         const double *cx = m.cxyz + 24 * (size_t)c + 3 * lv;
         D3 xv{cx[0], cx[1], cx[2]};
         const double av = A.vert_alpha[8 * (size_t)c + lv];
-        const D3 xm = 0.125 * grp_sum3(xv);
-        xv = xv - xm;
-        DFace f;
-        f.active = face_on;
-        f.planar = (m.cflags[c] >> min(lv, 5)) & 1;
-        f.fwd = fwd;
+        // the face's adjoint weight: zero unless the flux leaves the cell
+        const int32_t sv = face_on ? m.lface[6 * (size_t)c + lv] : kEmpty;
+        double wgt = 0.0;
+        if (sv != kEmpty) {
+            const int32_t fid = sv >= 0 ? sv : ~sv;
+            const double ph = A.phi[fid];
+            if ((sv >= 0 ? ph : -ph) > 0.0) wgt = A.w.vbar[fid];
+        }
+        xv = xv - 0.125 * grp_sum3(xv);
+        D3 q[4];
+        int wet = 0, ids = 0;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            f.q[i] = D3{grp_get(xv.x, fv[i]), grp_get(xv.y, fv[i]), grp_get(xv.z, fv[i])};
-            f.aq[i] = Dl{grp_get(av, fv[i]), fv[i] == dir ? 1.0 : 0.0};
+            q[i] = D3{grp_get(xv.x, fv[i]), grp_get(xv.y, fv[i]), grp_get(xv.z, fv[i])};
+            wet |= (grp_get(av, fv[i]) > iso ? 1 : 0) << i;
+            ids |= fv[i] << (4 * i);
         }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const Dl d = ((fwd >> i) & 1) ? f.aq[(i + 1) & 3] - f.aq[i] : f.aq[i] - f.aq[(i + 1) & 3];
-            f.inv[i] = d.v != 0.0 ? dinv(d) : dc(0.0);
+        if (!face_on) wet = 0;
+        // the face's isoface edges: one, or two on a saddle
+        const int entries = ~wet & ((wet >> 1) | (wet << 3)) & 15;
+        auto iso_edge = [&](int on) {
+            IsoEdge S;
+            S.on = on != 0;
+            const int e = S.on ? __ffs(on) - 1 : 0;  // loop position of the dry end
+            const int l = (wet >> ((e + 3) & 3)) & 1 ? e + 3 : ((wet >> ((e + 2) & 3)) & 1 ? e + 2 : e + 1);
+            auto id = [&](int i) { return (ids >> (4 * (i & 3))) & 15; };
+            S.dn = id(e);
+            S.n = id(e + 1);
+            S.x = id(l);
+            S.dx = id(l + 1);
+            auto at = [&](int v) { return D3{grp_get(xv.x, v), grp_get(xv.y, v), grp_get(xv.z, v)}; };
+            S.qn = at(S.n);
+            S.qx = at(S.x);
+            S.t0 = at(S.dn) - S.qn;
+            S.t1 = at(S.dx) - S.qx;
+            const double an = grp_get(av, S.n), ax = grp_get(av, S.x);
+            const double D0 = grp_get(av, S.dn) - an, D1 = grp_get(av, S.dx) - ax;
+            S.g0 = S.on ? 1.0 / D0 : 0.0;
+            S.g1 = S.on ? 1.0 / D1 : 0.0;
+            S.lam0 = (iso - an) * S.g0;
+            S.lam1 = (iso - ax) * S.g1;
+            S.s0 = S.qn + S.lam0 * S.t0;
+            S.s1 = S.qx + S.lam1 * S.t1;
+            return S;
+        };
+        const IsoEdge E0 = iso_edge(entries);
+        const bool saddles = __any((entries & (entries - 1)) != 0);
+        IsoEdge E1{};
+        if (saddles) E1 = iso_edge(entries & (entries - 1));
+        auto edges = [&](auto body) {
+            if (E0.on) body(E0, 0);
+            if (saddles && E1.on) body(E1, 1);
+        };
+        // the isoface's sums and apex
+        D3 cseg = Z, oacc = Z;
+        double oL = 0.0;
+        edges([&](const IsoEdge &S, int) {
+            const double l = norm3(S.s1 - S.s0);
+            cseg = cseg + cross(S.s0, S.s1);
+            oacc = oacc + (0.5 * l) * (S.s0 + S.s1);
+            oL += l;
+        });
+        const D3 lseg = cseg;  // the face's own
+        cseg = grp_sum3(cseg);
+        oacc = grp_sum3(oacc);
+        oL = grp_sum(oL);
+        D3 o = Z;
+        if (oL > 0.0) {
+            o = (1.0 / oL) * oacc;
+        } else {  // no edge has a length: the mean of their ends
+            D3 os = Z;
+            double ns = 0.0;
+            edges([&](const IsoEdge &S, int) {
+                os = os + S.s0;
+                ns += 1.0;
+            });
+            os = grp_sum3(os);
+            ns = grp_sum(ns);
+            if (ns > 0.0) o = (1.0 / ns) * os;
         }
-        const double iso = A.iso[c];
-        // one pass along this direction: the sub-volume's rate (at fixed isovalue for a vertex
-        // value, along the isovalue for direction 8), and the isoface and swept integrals
-        const Dl isod{iso, dir == 8 ? 1.0 : 0.0};
-        DV3 o, cseg;
-        const Dl g0 = dcell_vsub6(f, isod, &o, &cseg);
-        const Dl nrm = dnorm(cseg);
-        double contrib = 0.0;
-        if (nrm.v > 0.0) {
-            const DV3 nS = dinv(nrm) * cseg;
-            DV3 acc;
-            Dl ws;
-            dface_centre_part(f, isod, o, nS, acc, ws);
-            acc = dgrp_sum3(acc);
-            ws = dgrp_sum(ws);
-            const DV3 xS = dinv(3.0 * ws) * acc;
-            const Dl un = A.U[c] * nS.x + A.U[m.n_cells + c] * nS.y + A.U[2 * (size_t)m.n_cells + c] * nS.z;
-            if (f.active) {
-                const int32_t v = m.lface[6 * (size_t)c + lv];
-                if (v != kEmpty) {
-                    const int32_t fid = v >= 0 ? v : ~v;
-                    const double ph = A.phi[fid];
-                    const double out = v >= 0 ? ph : -ph;
-                    if (out > 0.0) {
-                        Dl dq[4];
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) dq[i] = ddot(dv(f.q[i]) - xS, nS);
-                        Dl accI = dc(0.0);
-                        double Af = 0.0;
-                        if (f.planar) {
-                            const double A1 = 0.5 * norm3(cross(f.q[1] - f.q[0], f.q[2] - f.q[0]));
-                            const double A2 = 0.5 * norm3(cross(f.q[2] - f.q[0], f.q[3] - f.q[0]));
-                            accI = A1 * dtri_sweep(dq[0], dq[1], dq[2], un, dtc) + A2 * dtri_sweep(dq[0], dq[2], dq[3], un, dtc);
-                            Af = A1 + A2;
-                        } else {
-                            const D3 ap = 0.25 * (f.q[0] + f.q[1] + f.q[2] + f.q[3]);
-                            const Dl dap = ddot(dv(ap) - xS, nS);
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) {
-                                const double Ai = 0.5 * norm3(cross(f.q[i] - ap, f.q[(i + 1) & 3] - ap));
-                                accI = accI + Ai * dtri_sweep(dap, dq[i], dq[(i + 1) & 3], un, dtc);
-                                Af += Ai;
-                            }
-                        }
-                        contrib = A.w.vbar[fid] * (accI.d / Af);
-                    }
+        // the wet part of the face: its area vector C (x2) and, on a face that is not planar, the apex
+        // over its loop; six times the sub-volume
+        D3 C = Z - lseg, ap = q[0], pacc = Z;
+        double pl = 0.0;
+        if (wet) {
+            auto side = [&](bool on, D3 u, D3 v) {
+                if (on) C = C + cross(u, v);
+                if (on && !planar) {
+                    const double l = norm3(v - u);
+                    pacc = pacc + (0.5 * l) * (u + v);
+                    pl += l;
                 }
-            }
+            };
+#pragma unroll
+            for (int i = 0; i < 4; ++i) side((wet >> i) & (wet >> ((i + 1) & 3)) & 1, q[i], q[(i + 1) & 3]);
+            edges([&](const IsoEdge &S, int) {
+                side(true, S.qx, S.s1);
+                side(true, S.s0, S.qn);
+                if (!planar) {
+                    const double l = norm3(S.s1 - S.s0);
+                    pacc = pacc + (0.5 * l) * (S.s0 + S.s1);
+                    pl += l;
+                }
+            });
+            if (!planar && pl > 0.0) ap = (1.0 / pl) * pacc;
         }
-        // this direction's rate of six times the sub-volume and of the faces' adjoint-weighted swept
-        // integrals; k_adj_points and k_adj_cells combine them (adj_vertex, adj_alpha)
-        const double gsum = grp_sum(contrib);
+        const double v6 = grp_sum(wet ? dot(ap, C) : 0.0) + dot(o, cseg);
+        const double nrm = norm3(cseg);
+        // cut adjoints along their edges: of G (yg) and of C (yc), entry and exit of each edge
+        double yg[2][2] = {{0.0, 0.0}, {0.0, 0.0}}, yc[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
+        D3 oab = Z, csb = Z;
+        double olb = 0.0;
+        const double invL = oL > 0.0 ? 1.0 / oL : 0.0;
+        if (nrm > 0.0) {
+            const D3 n = (1.0 / nrm) * cseg;
+            D3 acc = Z;
+            double ws = 0.0;
+            edges([&](const IsoEdge &S, int) {
+                const double wt = dot(cross(S.s0 - o, S.s1 - o), n);
+                acc = acc + wt * (o + S.s0 + S.s1);
+                ws += wt;
+            });
+            acc = grp_sum3(acc);
+            ws = grp_sum(ws);
+            const double inv3w = 1.0 / (3.0 * ws);
+            const D3 xS = inv3w * acc;
+            const double un = dot(U, n);
+            // the swept integrals' rates with the distances of the face's vertices and apex, and the speed
+            D3 xb = Z, nb = Z;
+            if (wgt != 0.0) {
+                const D3 B = sel3(planar, q[0], 0.25 * (q[0] + q[1] + q[2] + q[3]));
+                const double dB = dot(B - xS, n);
+                double d[4], area[4], db[4] = {0.0, 0.0, 0.0, 0.0}, dBb = 0.0, unb = 0.0, Af = 0.0;
+                D3 x[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) x[i] = sel3(planar, q[(i + 1) & 3], q[i]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    d[i] = dot(x[i] - xS, n);
+                    area[i] = i < 2 || !planar ? 0.5 * norm3(cross(x[i] - B, x[(i + 1) & 3] - B)) : 0.0;
+                    Af += area[i];
+                }
+#pragma unroll 1
+                for (int t = planar ? 2 : 4; t > 0; --t) {  // triangle (B, x0, x1), then the next
+                    const TriRates r = tri_rates(dB, d[0], d[1], un, dtc);
+                    dBb += area[0] * r.p0;
+                    unb += area[0] * r.pu;
+                    const double b0 = db[0] + area[0] * r.p1, b1 = db[1] + area[0] * r.p2;
+                    const double ta = area[0], td = d[0];
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) {
+                        area[i] = area[i + 1];
+                        d[i] = d[i + 1];
+                    }
+                    area[3] = ta;
+                    d[3] = td;
+                    db[0] = b1;
+                    db[1] = db[2];
+                    db[2] = db[3];
+                    db[3] = b0;
+                }
+                // (after two turns position i holds vertex i + 2, after four it holds vertex i)
+                const double wA = wgt / Af;
+                D3 sx = dBb * (B - xS);
+                double sd = dBb;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    sx = sx + db[i] * (sel3(planar, x[(i + 2) & 3], x[i]) - xS);
+                    sd += db[i];
+                }
+                nb = wA * (sx + unb * U);
+                xb = (-(wA * sd)) * n;
+            }
+            xb = grp_sum3(xb);
+            const D3 accb = inv3w * xb;
+            const double wsb = -3.0 * dot(accb, xS);
+            D3 ob = Z;
+            D3 c0[2] = {Z, Z}, c1[2] = {Z, Z};
+            edges([&](const IsoEdge &S, int k) {
+                const D3 P = S.s0 - o, Q = S.s1 - o, cr = cross(P, Q);
+                const double wt = dot(cr, n), wtb = dot(accb, o + S.s0 + S.s1) + wsb;
+                const D3 wa = wt * accb, pb = wtb * cross(Q, n), qb = wtb * cross(n, P);
+                c0[k] = wa + pb;
+                c1[k] = wa + qb;
+                ob = ob + wa - pb - qb;
+                nb = nb + wtb * cr;
+            });
+            ob = grp_sum3(ob);
+            nb = grp_sum3(nb);
+            oab = invL * ob;
+            olb = -dot(oab, o);
+            csb = (1.0 / nrm) * (nb - dot(n, nb) * n);
+            edges([&](const IsoEdge &S, int k) {
+                iso_edge_back(S, oab, olb, csb, c0[k], c1[k]);
+                yc[k][0] = dot(c0[k], S.t0);
+                yc[k][1] = dot(c1[k], S.t1);
+            });
+        }
+        // G: o . cseg, and each face's apex . C
+        const D3 goa = invL * cseg;
+        const double gol = -dot(goa, o);
+        const D3 pab = planar || !(pl > 0.0) ? Z : (1.0 / pl) * C;
+        const double plb = -dot(pab, ap);
+        edges([&](const IsoEdge &S, int k) {
+            D3 s0b = cross(ap, S.s1 - S.qn), s1b = cross(ap, S.qx - S.s0);
+            iso_edge_back(S, goa, gol, o, s0b, s1b);
+            if (!planar) {
+                auto side = [&](D3 u, D3 v, D3 &ub, D3 &vb) {
+                    const D3 d = v - u;
+                    const double l = norm3(d), lb = 0.5 * dot(pab, u + v) + plb, f = l > 0.0 ? lb / l : 0.0;
+                    ub = ub + 0.5 * l * pab - f * d;
+                    vb = vb + 0.5 * l * pab + f * d;
+                };
+                D3 fixed = Z;
+                side(S.qx, S.s1, fixed, s1b);
+                side(S.s1, S.s0, s1b, s0b);
+                side(S.s0, S.qn, s0b, fixed);
+            }
+            yg[k][0] = dot(s0b, S.t0);
+            yg[k][1] = dot(s1b, S.t1);
+        });
+        // to the isovalue and the vertex values: cut = wet end + lam t, lam = (iso - a_wet) / (a_dry - a_wet)
+        double gi = 0.0, ci = 0.0;
+        double gv[8], cv[8];
+#pragma unroll
+        for (int v = 0; v < 8; ++v) gv[v] = cv[v] = 0.0;
+        edges([&](const IsoEdge &S, int k) {
+            auto cut = [&](int w, int d, double lam, double rate, double y, double z) {
+                const double a = rate * y, b = rate * z;
+                gi += a;
+                ci += b;
+#pragma unroll
+                for (int v = 0; v < 8; ++v) {
+                    const double f = v == w ? lam - 1.0 : (v == d ? -lam : 0.0);
+                    gv[v] += f * a;
+                    cv[v] += f * b;
+                }
+            };
+            cut(S.n, S.dn, S.lam0, S.g0, yg[k][0], yc[k][0]);
+            cut(S.x, S.dx, S.lam1, S.g1, yg[k][1], yc[k][1]);
+        });
+        gi = grp_sum(gi);
+        ci = grp_sum(ci);
+        double G = 0.0, Cv = 0.0;  // vertex lv's
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+            const double a = grp_sum(gv[v]), b = grp_sum(cv[v]);
+            G = v == lv ? a : G;
+            Cv = v == lv ? b : Cv;
+        }
+        // The isovalue moves with the volume constraint, so the adjoint of vertex value v is its rate at
+        // fixed isovalue plus the isovalue's rate along v, -G_v / G_iso, times the rate along the
+        // isovalue; alpha_P's is V6 / G_iso times that.  At a jump of the sub-volume the isovalue is the
+        // jumping vertex's value and moves with it (rate 1 for that one, 0 otherwise and for alpha_P).
+        const bool jump = fabs(v6 - aP * V6) > 1e-9 * V6;
+        const uint64_t hit = __ballot(jump && av == iso);
+        const int mvert = (int)((hit >> (__lane_id() & ~(kLanes - 1))) & 0xFF);
+        double xdot, adot;
+        if (jump) {
+            xdot = mvert && __ffs(mvert) - 1 == lv ? 1.0 : 0.0;
+            adot = 0.0;
+        } else {
+            xdot = gi != 0.0 ? -G / gi : 0.0;
+            adot = gi != 0.0 ? V6 / gi : 0.0;
+        }
         double *gb = A.w.gbuf + (size_t)kAdjG * c;
-        if (lv == 0) {
-            gb[dir] = g0.d;
-            gb[9 + dir] = gsum;
-        }
-        if (dir == 8) {
-            // at a jump of the sub-volume the isovalue is a vertex value and moves with it
-            const bool jump = fabs(g0.v - aP * V6) > 1e-9 * V6;
-            const uint64_t hit = __ballot(jump && av == iso);
-            const int mvert = (int)((hit >> (__lane_id() & ~(kLanes - 1))) & 0xFF);
-            if (lv == 0) {
-                gb[18] = jump ? (double)(mvert ? __ffs(mvert) - 1 : -1) : -2.0;
-                gb[19] = V6;
-            }
-        }
+        gb[lv] = Cv + xdot * ci;
+        if (lv == 0) gb[8] = adot * ci;
     }
-}
-
-// The isovalue moves with the volume constraint, so the adjoint of vertex value v is its rate at
-// fixed isovalue plus the isovalue's rate along v times the rate along the isovalue: with G the
-// rates of six times the sub-volume and C those of the adjoint-weighted swept integrals,
-// iso' = -G_v / G_iso, and alpha_P's is iso' = V6 / G_iso times C_iso.  At a jump the isovalue is
-// the jumping vertex's value (iso' = 1 for it, 0 otherwise, and 0 for alpha_P).
-__device__ __forceinline__ double adj_vertex(const double *gb, int v) {
-    const double jump = gb[18], gx = gb[8];
-    double xdot;
-    if (jump > -2.0) xdot = (double)v == jump ? 1.0 : 0.0;
-    else xdot = gx != 0.0 ? -gb[v] / gx : 0.0;
-    return gb[9 + v] + xdot * gb[17];
-}
-__device__ __forceinline__ double adj_alpha(const double *gb) {
-    const double gx = gb[8];
-    const double xdot = gb[18] > -2.0 ? 0.0 : (gx != 0.0 ? gb[19] / gx : 0.0);
-    return xdot * gb[17];
 }
 
 // ------------------------------------------------------------------ general polyhedra (16 lanes)
@@ -1141,7 +1228,7 @@ __global__ void __launch_bounds__(256) k_adj_points(AdjArgs A) {
             }
 #pragma unroll
             for (int v = 0; v < 8; ++v)
-                if (m.cpt[8 * (size_t)c + v] == k) sum += adj_vertex(A.w.gbuf + (size_t)kAdjG * c, v);
+                if (m.cpt[8 * (size_t)c + v] == k) sum += A.w.gbuf[(size_t)kAdjG * c + v];
         }
     }
     A.w.pbar[k] = sum;
@@ -1170,7 +1257,7 @@ __global__ void __launch_bounds__(256) k_adj_cells(AdjArgs A) {
         A.abar[c] = acc;
         return;
     }
-    if (A.kind[c] == 1) acc += adj_alpha(A.w.gbuf + (size_t)kAdjG * c);
+    if (A.kind[c] == 1) acc += A.w.gbuf[(size_t)kAdjG * c + 8];
     int32_t cls[8];
     double pb[8];
 #pragma unroll
@@ -1203,8 +1290,8 @@ hipError_t launch_adj_w(const AdjArgs &a, hipStream_t s) {
         hipLaunchKernelGGL(k_adj_unsweep_correct<W>, dim3(gb), dim3(256), 0, s, a, it);
     }
     hipLaunchKernelGGL(k_adj_faces<W>, dim3(g), dim3(256), 0, s, a);
-    const int gs = std::max(1, std::min(2048, (int)((9L * n * kLanes + 255) / 256)));
-    hipLaunchKernelGGL(k_adj_surface, dim3(gs), dim3(256), 0, s, a);
+    const int gs = std::max(1, std::min(4096, (int)(((long)n * kLanes + 63) / 64)));
+    hipLaunchKernelGGL(k_adj_surface, dim3(gs), dim3(64), 0, s, a);
     if (a.m.cbig) {
         const int gb = std::max(1, std::min(1024, (int)((33L * a.w.big_cap + kBGrpPerBlock - 1) / kBGrpPerBlock)));
         hipLaunchKernelGGL(k_adj_surface_big, dim3(gb), dim3(kBGrp * kBGrpPerBlock), 0, s, a);

@@ -184,10 +184,10 @@ struct Params {
 
 // Adjoint workspace (device pointers; allocated by a plan on its first adjoint step).  S = number of
 // bounding sweeps (at least 1), nc cells, nf faces.
-// adjoint counters: the interface cells' (cell, direction) pairs to differentiate along, then per
-// sweep s the length of its list of
+// adjoint counters: the interface cells, the polyhedra's (cell, direction) pairs to differentiate
+// along, then per sweep s the length of its list of
 // cells out of bounds (kAdjL + s) and of the cells its corrections touch (kAdjT + s)
-enum : int { kAdjDirs = 2, kAdjDirsBig = 3, kAdjGBig = 68, kAdjL = 8, kAdjT = 40, kAdjNum = 72, kAdjMaxSweeps = 31, kAdjG = 20,
+enum : int { kAdjCells = 2, kAdjDirsBig = 3, kAdjGBig = 68, kAdjL = 8, kAdjT = 40, kAdjNum = 72, kAdjMaxSweeps = 31, kAdjG = 9,
              kAdjBoundBlocks = 512 };
 struct AdjWork {
     int32_t *counters = nullptr;  // [kAdjNum]
@@ -208,10 +208,10 @@ struct AdjWork {
     double *dvcurbar = nullptr;   // [nf]
     double *deltabar = nullptr;   // [nf]
     double *vbar = nullptr;       // [nf] adjoint of the swept integral of interface-upwind faces, times phi
-    double *gbuf = nullptr;       // [kAdjG nc] reconstructed cells: rates along their 8 vertex values and the
-                                  // isovalue (see adjoint.hip)
+    double *gbuf = nullptr;       // [kAdjG nc] reconstructed cells: adjoints of their 8 vertex values and of
+                                  // alpha through the isoface
     double *pbar = nullptr;       // [n_classes] adjoint of each point class's vertex value
-    int64_t *dlist = nullptr;     // [9 nc] (cell << 4 | direction) pairs of the interface cells
+    int32_t *clist = nullptr;     // [nc] reconstructed cells other than general polyhedra
     // general polyhedra: (cell << 6 | direction) pairs, and the rates per polyhedron
     int64_t *dlist_big = nullptr;  // [33 n_big]
     double *gbig = nullptr;        // [kAdjGBig n_big]

@@ -1294,7 +1294,7 @@ static iso_status adj_alloc(iso_plan *p) {
         alloc((void **)&w.dVb, nf * 8) && alloc((void **)&w.phib, nf * 8) && alloc((void **)&w.dvcurbar, nf * 8) &&
         alloc((void **)&w.deltabar, nf * 8) && alloc((void **)&w.vbar, nf * 8) &&
         alloc((void **)&w.gbuf, kAdjG * nc * 8) && alloc((void **)&w.pbar, std::max<size_t>(m->n_classes, 1) * 8) &&
-        alloc((void **)&w.dlist, 9 * nc * 8) &&
+        alloc((void **)&w.clist, nc * 4) &&
         alloc((void **)&w.dlist_big, 33 * std::max<size_t>(m->n_big, 1) * 8) &&
         alloc((void **)&w.gbig, kAdjGBig * std::max<size_t>(m->n_big, 1) * 8) &&
         alloc((void **)&p->adj_vert, 8 * nc * 8) && alloc((void **)&p->adj_kind, nc * 4) &&
