@@ -295,7 +295,9 @@ template <int W>
 __global__ void __launch_bounds__(256) k_adj_prep(AdjArgs A) {
     const int n = A.m.n_cells;
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    for (int64_t f = c; f < A.m.n_faces; f += (int64_t)gridDim.x * blockDim.x) A.phibar[f] = 0.0;
+    // (a linear pass over the faces: through each cell's own slots it took 28.2 us, not 20.8, on 128x64x64)
+    for (int64_t f = c; f < A.m.n_faces; f += (int64_t)gridDim.x * blockDim.x)
+        A.phibar[f] = A.w.dVb[f] = A.w.phib[f] = A.w.dvcurbar[f] = 0.0;
     bool offend = false;
     double x = 0.0;
     if (c < n) {
@@ -312,15 +314,6 @@ __global__ void __launch_bounds__(256) k_adj_prep(AdjArgs A) {
         A.w.xbar[c] = xb;
         A.w.pv[c] = raw_chopped(A.raw[c], A.clip, A.tol) ? 0.0 : xb / A.m.vol[c];
         A.w.cflag[c] = clamped ? 1 : 0;
-#pragma unroll
-        for (int k = 0; k < W; ++k) {
-            const int32_t v = A.m.slot_face[(size_t)k * n + c];
-            if (v != kEmpty && v >= 0) {
-                A.w.dVb[v] = 0.0;
-                A.w.phib[v] = 0.0;
-                A.w.dvcurbar[v] = 0.0;
-            }
-        }
     }
     if (A.n_iter < 1) return;  // uniform
     const int row = block_append(offend ? 1 : 0, &A.w.counters[kAdjL]);
@@ -334,18 +327,22 @@ __global__ void __launch_bounds__(256) k_adj_prep(AdjArgs A) {
     adj_append_touched<W>(A, 0, tsel);
 }
 
+// A list's length (atomics filled it, perhaps in this kernel: not through the L1).
+__device__ __forceinline__ int adj_count(const AdjArgs &A, int i) {
+    return __hip_atomic_load(&A.w.counters[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Phase B of sweep s: every touched cell applies its faces' corrections in ascending face order
 // (round-off chop; clamp on the last sweep); a cell still out of bounds runs phase A of sweep s+1.
 template <int W>
-__global__ void __launch_bounds__(256) k_adj_sweep(AdjArgs A, int s) {
+__device__ __forceinline__ void adj_sweep(const AdjArgs &A, int s, int b0, int stride) {
     const int n = A.m.n_cells, nf = A.m.n_faces;
     const DevMesh &m = A.m;
     const AdjWork &w = A.w;
-    const int stride = gridDim.x * blockDim.x;
-    const int t0 = blockIdx.x * blockDim.x + threadIdx.x;
+    const int t0 = b0 + threadIdx.x;
     const bool last = s == A.n_iter - 1;
     if (s >= 1) {  // sweep s-1's corrections were read by the previous kernel: clear them
-        const int np = w.counters[kAdjL + s - 1];
+        const int np = adj_count(A, kAdjL + s - 1);
         double *stale = w.delta + (size_t)((s - 1) % 3) * nf;
         for (int i = t0; i < np; i += stride) {
             const int32_t P = w.list[(size_t)(s - 1) * n + i];
@@ -362,9 +359,9 @@ __global__ void __launch_bounds__(256) k_adj_sweep(AdjArgs A, int s) {
     const int32_t *T = w.tlist + (size_t)s * n;
     int32_t *mark = w.cmark + (size_t)(s & 1) * n;
     int32_t *mark_next = w.cmark + (size_t)((s + 1) & 1) * n;
-    const int nT = w.counters[kAdjT + s];
-    const int nloop = (nT + 255) & ~255;  // whole work-groups iterate together
-    for (int i0 = blockIdx.x * blockDim.x; i0 < nloop; i0 += stride) {
+    const int nT = adj_count(A, kAdjT + s), bd = blockDim.x;
+    const int nloop = (nT + bd - 1) / bd * bd;  // whole work-groups iterate together
+    for (int i0 = b0; i0 < nloop; i0 += stride) {
         const int i = i0 + threadIdx.x;
         bool again = false;
         int32_t Q = 0;
@@ -409,13 +406,11 @@ __global__ void __launch_bounds__(256) k_adj_sweep(AdjArgs A, int s) {
 // chopped cells' adjoints zeroed.  The two sets are disjoint, so one kernel does both.  The forward
 // replay is over: its face marks and this sweep's corrections are cleared here.
 template <int W>
-__global__ void __launch_bounds__(256) k_adj_unsweep_apply(AdjArgs A, int s) {
+__device__ __forceinline__ void adj_unsweep_apply(const AdjArgs &A, int s, int t0, int stride) {
     const int n = A.m.n_cells, nf = A.m.n_faces;
     const DevMesh &m = A.m;
     const AdjWork &w = A.w;
-    const int stride = gridDim.x * blockDim.x;
-    const int t0 = blockIdx.x * blockDim.x + threadIdx.x;
-    const int nl = w.counters[kAdjL + s], nt = w.counters[kAdjT + s];
+    const int nl = adj_count(A, kAdjL + s), nt = adj_count(A, kAdjT + s);
     const int32_t *L = w.list + (size_t)s * n;
     const int32_t *T = w.tlist + (size_t)s * n;
     double *delta = w.delta + (size_t)(s % 3) * nf;
@@ -449,15 +444,14 @@ __global__ void __launch_bounds__(256) k_adj_unsweep_apply(AdjArgs A, int s) {
 // Reverse of sweep s, second half: through the corrections of each listed cell, to its bounding
 // state, its outflow faces' fluxes and their dV (before bounding, or running from an earlier sweep).
 template <int W>
-__global__ void __launch_bounds__(256) k_adj_unsweep_correct(AdjArgs A, int s) {
+__device__ __forceinline__ void adj_unsweep_correct(const AdjArgs &A, int s, int t0, int stride) {
     constexpr int R = 4 + 2 * W;
     const int n = A.m.n_cells;
     const DevMesh &m = A.m;
     const AdjWork &w = A.w;
-    const int stride = gridDim.x * blockDim.x;
-    const int nl = w.counters[kAdjL + s];
+    const int nl = adj_count(A, kAdjL + s);
     const int32_t *L = w.list + (size_t)s * n;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nl; i += stride) {
+    for (int i = t0; i < nl; i += stride) {
         const int32_t P = L[i];
         const uint64_t flags = w.tflag[(size_t)s * n + i];
         const double *rec = w.tape + ((size_t)s * n + i) * R;
@@ -509,11 +503,63 @@ __global__ void __launch_bounds__(256) k_adj_unsweep_correct(AdjArgs A, int s) {
     }
 }
 
+// The sweeps on the grid, and all from `first` on, forwards and back, in one work-group: their lists are
+// short, and what they cost is their launches (see k_bound_group of the step, whose lists they are).
+// A traced step and adjoint of 128x64x64 cells and the gradient of five 256x128 slab steps: nine launches
+// 252 and 845 us, with this (and the gathers of k_adj_faces straight-line) 221 and 750.
+template <int W>
+__global__ void __launch_bounds__(256) k_adj_sweep(AdjArgs A, int s) {
+    adj_sweep<W>(A, s, blockIdx.x * blockDim.x, gridDim.x * blockDim.x);
+}
+template <int W>
+__global__ void __launch_bounds__(256) k_adj_unsweep_apply(AdjArgs A, int s) {
+    adj_unsweep_apply<W>(A, s, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
+}
+template <int W>
+__global__ void __launch_bounds__(256) k_adj_unsweep_correct(AdjArgs A, int s) {
+    adj_unsweep_correct<W>(A, s, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
+}
+template <int W>
+__global__ void __launch_bounds__(bound_threads(W)) k_adj_group(AdjArgs A, int first) {
+    const int t = threadIdx.x, nt = blockDim.x;
+    for (int s = first; s < A.n_iter; ++s) {
+        adj_sweep<W>(A, s, 0, nt);
+        __syncthreads();
+    }
+    for (int s = A.n_iter - 1; s >= first; --s) {
+        adj_unsweep_apply<W>(A, s, t, nt);
+        __syncthreads();
+        adj_unsweep_correct<W>(A, s, t, nt);
+        __syncthreads();
+    }
+}
+
 // per cell: transposes of the update (through the round-off chop) and of the bulk fluxes
 template <int W>
 __device__ __forceinline__ void adj_faces_cell(const AdjArgs &A, int c) {
     const int n = A.m.n_cells;
     const DevMesh &m = A.m;
+    // all loads of one kind together, none behind a branch (an empty slot reads the last face, a
+    // boundary one cell 0): 43.1 -> 23.7 us on 128x64x64 cells
+    int32_t v[W], o[W];
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+        v[k] = m.slot_face[(size_t)k * n + c];
+        o[k] = m.slot_nbr[(size_t)k * n + c];
+    }
+    double ph[W], db[W], pv[W], d0[W], pb[W];
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+        const int32_t f = min(face_of(v[k]), m.n_faces - 1);
+        ph[k] = A.phi[f];
+        db[k] = A.w.dVb[f];
+        pv[k] = A.w.pv[max(o[k], 0)];
+        d0[k] = pb[k] = 0.0;
+        if (v[k] >= 0) {
+            d0[k] = A.dV0[f];
+            pb[k] = A.w.phib[f];
+        }
+    }
     // adjoint of the update before its round-off chop, and the same over the volume (kept per cell
     // by the kernels that change it, so a neighbour costs one load)
     const double bc = raw_chopped(A.raw[c], A.clip, A.tol) ? 0.0 : A.w.xbar[c];
@@ -523,22 +569,16 @@ __device__ __forceinline__ void adj_faces_cell(const AdjArgs &A, int c) {
     double acc = bc;
 #pragma unroll
     for (int k = 0; k < W; ++k) {
-        const int32_t v = m.slot_face[(size_t)k * n + c];
-        if (v == kEmpty) continue;
-        const int32_t f = v >= 0 ? v : ~v;
-        const int32_t o = m.slot_nbr[(size_t)k * n + c];
-        const double ph = A.phi[f];
+        if (v[k] == kEmpty) continue;
+        const int32_t f = face_of(v[k]);
         // alpha_raw(owner) -= dV/V_owner, alpha_raw(neighbour) += dV/V_neighbour
-        double dvb;
-        if (v >= 0) dvb = -bc / Vc + (o >= 0 ? A.w.pv[o] : 0.0);
-        else dvb = -(o >= 0 ? A.w.pv[o] : 0.0) + bc / Vc;
-        dvb += A.w.dVb[f];
-        const double out = v >= 0 ? ph : -ph;
-        if (out > 0.0) {
-            if (recon) A.w.vbar[f] = dvb * ph;  // dV = phi * (swept integral of the interface cell)
-            else acc += dvb * ph * dtc;         // dV = alpha_c phi dt
+        const double po = o[k] >= 0 ? pv[k] : 0.0;
+        const double dvb = (v[k] >= 0 ? -bc / Vc + po : -po + bc / Vc) + db[k];
+        if (seen_from(v[k], ph[k]) > 0.0) {
+            if (recon) A.w.vbar[f] = dvb * ph[k];  // dV = phi * (swept integral of the interface cell)
+            else acc += dvb * ph[k] * dtc;         // dV = alpha_c phi dt
         }
-        if (v >= 0) A.phibar[f] = (ph != 0.0 ? dvb * (A.dV0[f] / ph) : 0.0) + A.w.phib[f];
+        if (v[k] >= 0) A.phibar[f] = (ph[k] != 0.0 ? dvb * (d0[k] / ph[k]) : 0.0) + pb[k];
     }
     A.abar[c] = acc;
 }
@@ -1284,8 +1324,10 @@ hipError_t launch_adj_w(const AdjArgs &a, hipStream_t s) {
     const int g = (n + 255) / 256;
     const int gb = std::max(1, std::min(g, (int)kAdjBoundBlocks));
     hipLaunchKernelGGL(k_adj_prep<W>, dim3(g), dim3(256), 0, s, a);
-    for (int it = 0; it < a.n_iter; ++it) hipLaunchKernelGGL(k_adj_sweep<W>, dim3(gb), dim3(256), 0, s, a, it);
-    for (int it = a.n_iter - 1; it >= 0; --it) {
+    const int grid = std::min(a.n_iter, n <= kBoundGroupCells ? 0 : 1);  // sweeps over the whole grid
+    for (int it = 0; it < grid; ++it) hipLaunchKernelGGL(k_adj_sweep<W>, dim3(gb), dim3(256), 0, s, a, it);
+    if (grid < a.n_iter) hipLaunchKernelGGL(k_adj_group<W>, dim3(1), dim3(bound_threads(W)), 0, s, a, grid);
+    for (int it = grid - 1; it >= 0; --it) {
         hipLaunchKernelGGL(k_adj_unsweep_apply<W>, dim3(gb), dim3(256), 0, s, a, it);
         hipLaunchKernelGGL(k_adj_unsweep_correct<W>, dim3(gb), dim3(256), 0, s, a, it);
     }

@@ -139,6 +139,13 @@ __device__ __forceinline__ double grp_sum(double v) {
 __device__ __forceinline__ D3 grp_sum3(D3 v) { return D3{grp_sum(v.x), grp_sum(v.y), grp_sum(v.z)}; }
 __device__ __forceinline__ double grp_get(double v, int src) { return __shfl(v, src, 8); }
 
+// The face of a slot, and a quantity of the face as seen from the slot's cell (its sign turned on
+// the neighbour's side).
+__device__ __forceinline__ int32_t face_of(int32_t v) { return v ^ (v >> 31); }
+__device__ __forceinline__ double seen_from(int32_t v, double q) {
+    return __hiloint2double(__double2hiint(q) ^ (int)(v & 0x80000000), __double2loint(q));
+}
+
 // The flux of face f and the velocity of cell c; with a second time level (outer iterations,
 // Crank-Nicolson) their averages, formed as they are read.
 template <bool kAvg>

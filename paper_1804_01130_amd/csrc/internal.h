@@ -182,6 +182,11 @@ struct Params {
     double root_tol;  // isovalue search stops at |V_sub/V - alpha| <= root_tol (0: to round-off)
 };
 
+// Bounding sweeps in one work-group: up to this many cells all of them, and its threads for W flux slots
+// (k_bound_group has the reasons).
+constexpr int kBoundGroupCells = 1 << 17;
+constexpr int bound_threads(int W) { return W > 8 ? 512 : 1024; }
+
 // Adjoint workspace (device pointers; allocated by a plan on its first adjoint step).  S = number of
 // bounding sweeps (at least 1), nc cells, nf faces.
 // adjoint counters: the interface cells, the polyhedra's (cell, direction) pairs to differentiate

@@ -897,13 +897,6 @@ __device__ __forceinline__ int32_t *dlist_buf(const DevWork &w, int s, int nf) {
     return w.flist + (size_t)(1 + s % 3) * nf;
 }
 
-// The face of a slot, and a quantity of the face as seen from the slot's cell (its sign turned on
-// the neighbour's side).
-__device__ __forceinline__ int32_t face_of(int32_t v) { return v ^ (v >> 31); }
-__device__ __forceinline__ double seen_from(int32_t v, double q) {
-    return __hiloint2double(__double2hiint(q) ^ (int)(v & 0x80000000), __double2loint(q));
-}
-
 // W flux slots per cell, all loads of one kind issued together (independent gathers in flight).
 // Bound by the L1: 330 line look-ups a wave, and as long again held up by look-ups of lines still on
 // their way (own face fluxes are interleaved, so three slots ask for the same lines).  Straight-line
@@ -1117,10 +1110,6 @@ __global__ void __launch_bounds__(update_threads(W)) k_update(UpdArgs A) {
     for (int k = 0; k <= W; ++k)
         if ((tsel >> k) & 1) A.w.tlist[bt++] = k < W ? o[k < W ? k : 0] : c;
 }
-
-// (see k_bound_group)
-constexpr int kBoundGroupCells = 1 << 17;
-constexpr int bound_threads(int W) { return W > 8 ? 512 : 1024; }
 
 struct BoundArgs {
     DevMesh m;
