@@ -190,31 +190,41 @@ __device__ __forceinline__ void adj_correct(const AdjArgs &A, int s, int32_t P, 
     const AdjWork &w = A.w;
     const bool over = a > 1.0 + A.tol;
     const double dtc = cell_dt(m, A.dt_dom, A.dt, P);
-    int32_t v[W], fid[W];
-    double ph[W], cap[W], dvnow[W];
+    // all loads of one kind together, none behind a branch (an empty slot reads the last face)
+    const double vP = m.vol[P];
+    int32_t v[W], fid[W], nb[W], tch[W];
+    double ph[W], cap[W], dvnow[W], dv0[W];
 #pragma unroll
     for (int k = 0; k < W; ++k) {
-        v[k] = m.slot_pair[(size_t)P * W + k].x;
-        fid[k] = v[k] >= 0 ? v[k] : ~v[k];
-        ph[k] = v[k] != kEmpty ? A.phi[fid[k]] : 0.0;
+        const int2 q = m.slot_pair[(size_t)P * W + k];
+        v[k] = q.x;
+        nb[k] = q.y;
+        fid[k] = min(face_of(v[k]), nf - 1);
+    }
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+        ph[k] = A.phi[fid[k]];
+        tch[k] = w.touched[fid[k]];
+        dvnow[k] = w.dvcur[fid[k]];
+        dv0[k] = A.dV0[fid[k]];
     }
     uint64_t flags = over ? 1 : 0;
     double sumcap = 0.0;
 #pragma unroll
     for (int k = 0; k < W; ++k) {
         cap[k] = 0.0;
-        dvnow[k] = 0.0;
-        if (v[k] == kEmpty) continue;
-        const double outphi = v[k] >= 0 ? ph[k] : -ph[k];
-        if (!(outphi > 0.0)) continue;
-        const bool tch = w.touched[fid[k]] != 0;
-        if (tch) flags |= kTouchedBit << k;
-        dvnow[k] = tch ? w.dvcur[fid[k]] : A.dV0[fid[k]];
-        const double outv = v[k] >= 0 ? dvnow[k] : -dvnow[k];
+        const double outphi = seen_from(v[k], ph[k]);
+        if (v[k] == kEmpty || !(outphi > 0.0)) {
+            dvnow[k] = 0.0;
+            continue;
+        }
+        if (tch[k]) flags |= kTouchedBit << k;
+        else dvnow[k] = dv0[k];
+        const double outv = seen_from(v[k], dvnow[k]);
         cap[k] = over ? outphi * dtc - outv : outv;
         if (cap[k] > 0.0) sumcap += cap[k];
     }
-    const double need = over ? (a - 1.0) * m.vol[P] : -a * m.vol[P];
+    const double need = over ? (a - 1.0) * vP : -a * vP;
     double r = 0.0;
     if (sumcap > 0.0) {
         flags |= 4;
@@ -229,12 +239,11 @@ __device__ __forceinline__ void adj_correct(const AdjArgs &A, int s, int32_t P, 
         if (!(sumcap > 0.0) || !(cap[k] > 0.0)) continue;
         flags |= kCorrBit << k;
         const double d = cap[k] * r;
-        const double dd = over ? (v[k] >= 0 ? d : -d) : (v[k] >= 0 ? -d : d);
+        const double dd = seen_from(v[k], over ? d : -d);
         delta[fid[k]] = dd;
         w.dvcur[fid[k]] = dvnow[k] + dd;
         w.touched[fid[k]] = 1;
-        const int32_t o = m.slot_pair[(size_t)P * W + k].y;
-        if (o >= 0 && atomicExch(&mark[o], 1) == 0) tsel[k] = o;
+        if (nb[k] >= 0 && atomicExch(&mark[nb[k]], 1) == 0) tsel[k] = nb[k];
     }
     double *rec = w.tape + ((size_t)s * n + row) * R;
     rec[0] = a;
@@ -368,15 +377,18 @@ __device__ __forceinline__ void adj_sweep(const AdjArgs &A, int s, int b0, int s
         double x = 0.0;
         if (i < nT) {
             Q = T[i];
+            const double aq = w.x[Q], vq = m.vol[Q];
+            int32_t v[W];
+            double d[W];
+#pragma unroll
+            for (int k = 0; k < W; ++k) v[k] = m.slot_pair[(size_t)Q * W + k].x;
+#pragma unroll
+            for (int k = 0; k < W; ++k) d[k] = delta[min(face_of(v[k]), nf - 1)];
             double sum = 0.0;
 #pragma unroll
-            for (int k = 0; k < W; ++k) {
-                const int32_t vq = m.slot_pair[(size_t)Q * W + k].x;
-                if (vq == kEmpty) continue;
-                const double d = delta[vq >= 0 ? vq : ~vq];
-                sum += vq >= 0 ? d : -d;
-            }
-            const double x0 = w.x[Q] - sum / m.vol[Q];
+            for (int k = 0; k < W; ++k)
+                if (v[k] != kEmpty) sum += seen_from(v[k], d[k]);
+            const double x0 = aq - sum / vq;
             x = x0;
             if (A.clip) {
                 if (x < 0.0 && x >= -A.tol) x = 0.0;
@@ -417,16 +429,27 @@ __device__ __forceinline__ void adj_unsweep_apply(const AdjArgs &A, int s, int t
     for (int i = t0; i < nl; i += stride) {
         const int32_t P = L[i];
         const uint64_t flags = w.tflag[(size_t)s * n + i];
+        const int32_t cP = w.cflag[P];
+        const double xP = w.xbar[P], vP = m.vol[P];
+        int2 q[W];
+        int32_t co[W];
+        double xo[W], vo[W];
+#pragma unroll
+        for (int k = 0; k < W; ++k) q[k] = m.slot_pair[(size_t)P * W + k];
+#pragma unroll
+        for (int k = 0; k < W; ++k) {
+            const int32_t o = max(q[k].y, 0);
+            co[k] = w.cflag[o];
+            xo[k] = w.xbar[o];
+            vo[k] = m.vol[o];
+        }
 #pragma unroll
         for (int k = 0; k < W; ++k) {
             if (!(flags & (kCorrBit << k))) continue;
-            const int2 q = m.slot_pair[(size_t)P * W + k];
-            const int32_t v = q.x, o = q.y;
-            const int32_t f = v >= 0 ? v : ~v;
-            const double sP = v >= 0 ? 1.0 : -1.0;
+            const int32_t f = face_of(q[k].x);
             double db = 0.0;
-            if (!(w.cflag[P] & (1 << s))) db -= sP * w.xbar[P] / m.vol[P];
-            if (o >= 0 && !(w.cflag[o] & (1 << s))) db += sP * w.xbar[o] / m.vol[o];
+            if (!(cP & (1 << s))) db -= seen_from(q[k].x, xP) / vP;
+            if (q[k].y >= 0 && !(co[k] & (1 << s))) db += seen_from(q[k].x, xo[k]) / vo[k];
             w.deltabar[f] = db;
             w.touched[f] = 0;
             delta[f] = 0.0;
@@ -458,6 +481,22 @@ __device__ __forceinline__ void adj_unsweep_correct(const AdjArgs &A, int s, int
         const bool over = flags & 1;
         const double sumcap = rec[2], r = rec[3];
         const double dtc = cell_dt(m, A.dt_dom, A.dt, P);
+        const double xP = w.xbar[P], vP = m.vol[P], raw = A.raw[P];
+        int32_t v[W], fid[W];
+        double cap[W], dlb[W], dvb[W], dV0b[W], phb[W];
+#pragma unroll
+        for (int k = 0; k < W; ++k) {
+            cap[k] = rec[4 + k];
+            v[k] = m.slot_pair[(size_t)P * W + k].x;
+            fid[k] = min(face_of(v[k]), m.n_faces - 1);
+        }
+#pragma unroll
+        for (int k = 0; k < W; ++k) {
+            dlb[k] = w.deltabar[fid[k]];
+            dvb[k] = w.dvcurbar[fid[k]];
+            dV0b[k] = w.dVb[fid[k]];
+            phb[k] = w.phib[fid[k]];
+        }
         double capb[W], dvnb[W];
         double rb = 0.0;
 #pragma unroll
@@ -465,14 +504,11 @@ __device__ __forceinline__ void adj_unsweep_correct(const AdjArgs &A, int s, int
             capb[k] = 0.0;
             dvnb[k] = 0.0;
             if (!(flags & (kCorrBit << k))) continue;
-            const int32_t v = m.slot_pair[(size_t)P * W + k].x;
-            const int32_t f = v >= 0 ? v : ~v;
-            const double s_ = v >= 0 ? 1.0 : -1.0;
-            const double ddb = w.deltabar[f] + w.dvcurbar[f];
-            const double d_b = over ? s_ * ddb : -s_ * ddb;
+            const double ddb = dlb[k] + dvb[k];
+            const double d_b = seen_from(v[k], over ? ddb : -ddb);
             capb[k] = d_b * r;
-            rb += d_b * rec[4 + k];
-            dvnb[k] = w.dvcurbar[f];  // dvcur after = dV-now + correction
+            rb += d_b * cap[k];
+            dvnb[k] = dvb[k];  // dvcur after = dV-now + correction
         }
         double needb = 0.0, sumcapb = 0.0;
         if ((flags & 4) && !(flags & 2)) {
@@ -481,32 +517,31 @@ __device__ __forceinline__ void adj_unsweep_correct(const AdjArgs &A, int s, int
         }
 #pragma unroll
         for (int k = 0; k < W; ++k) {
-            const double capk = rec[4 + k];
-            if (!(capk > 0.0) || !(flags & 4)) continue;
-            const int32_t v = m.slot_pair[(size_t)P * W + k].x;
-            const int32_t f = v >= 0 ? v : ~v;
-            const double s_ = v >= 0 ? 1.0 : -1.0;
+            if (!(cap[k] > 0.0) || !(flags & 4)) continue;
+            const int32_t f = fid[k];
             const double cb = capb[k] + sumcapb;
             const double outvb = over ? -cb : cb;
-            if (over) w.phib[f] += cb * s_ * dtc;
-            dvnb[k] += s_ * outvb;
+            if (over) w.phib[f] = phb[k] + seen_from(v[k], cb) * dtc;
+            dvnb[k] += seen_from(v[k], outvb);
             if (flags & (kTouchedBit << k)) {
                 w.dvcurbar[f] = dvnb[k];
             } else {
-                w.dVb[f] += dvnb[k];
+                w.dVb[f] = dV0b[k] + dvnb[k];
                 w.dvcurbar[f] = 0.0;
             }
         }
-        const double xb = w.xbar[P] + needb * (over ? m.vol[P] : -m.vol[P]);
+        const double xb = xP + needb * (over ? vP : -vP);
         w.xbar[P] = xb;
-        w.pv[P] = raw_chopped(A.raw[P], A.clip, A.tol) ? 0.0 : xb / m.vol[P];
+        w.pv[P] = raw_chopped(raw, A.clip, A.tol) ? 0.0 : xb / vP;
     }
 }
 
 // The sweeps on the grid, and all from `first` on, forwards and back, in one work-group: their lists are
 // short, and what they cost is their launches (see k_bound_group of the step, whose lists they are).
 // A traced step and adjoint of 128x64x64 cells and the gradient of five 256x128 slab steps: nine launches
-// 252 and 845 us, with this (and the gathers of k_adj_faces straight-line) 221 and 750.
+// 252 and 845 us, with this (and the gathers of k_adj_faces straight-line) 221 and 750, with the loads of
+// a sweep's cell batched, none behind a branch, 205 and 660 (this kernel on the slab 18.3 -> 11.9; on the box
+// 18.0, with 1024 threads and their 128 registers 27.5).
 template <int W>
 __global__ void __launch_bounds__(256) k_adj_sweep(AdjArgs A, int s) {
     adj_sweep<W>(A, s, blockIdx.x * blockDim.x, gridDim.x * blockDim.x);
@@ -519,8 +554,9 @@ template <int W>
 __global__ void __launch_bounds__(256) k_adj_unsweep_correct(AdjArgs A, int s) {
     adj_unsweep_correct<W>(A, s, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
 }
+constexpr int adj_group_threads(int W) { return W > 8 ? 256 : W > 4 ? 512 : 1024; }  // (its registers fit)
 template <int W>
-__global__ void __launch_bounds__(bound_threads(W)) k_adj_group(AdjArgs A, int first) {
+__global__ void __launch_bounds__(adj_group_threads(W)) k_adj_group(AdjArgs A, int first) {
     const int t = threadIdx.x, nt = blockDim.x;
     for (int s = first; s < A.n_iter; ++s) {
         adj_sweep<W>(A, s, 0, nt);
@@ -1326,7 +1362,7 @@ hipError_t launch_adj_w(const AdjArgs &a, hipStream_t s) {
     hipLaunchKernelGGL(k_adj_prep<W>, dim3(g), dim3(256), 0, s, a);
     const int grid = std::min(a.n_iter, n <= kBoundGroupCells ? 0 : 1);  // sweeps over the whole grid
     for (int it = 0; it < grid; ++it) hipLaunchKernelGGL(k_adj_sweep<W>, dim3(gb), dim3(256), 0, s, a, it);
-    if (grid < a.n_iter) hipLaunchKernelGGL(k_adj_group<W>, dim3(1), dim3(bound_threads(W)), 0, s, a, grid);
+    if (grid < a.n_iter) hipLaunchKernelGGL(k_adj_group<W>, dim3(1), dim3(adj_group_threads(W)), 0, s, a, grid);
     for (int it = grid - 1; it >= 0; --it) {
         hipLaunchKernelGGL(k_adj_unsweep_apply<W>, dim3(gb), dim3(256), 0, s, a, it);
         hipLaunchKernelGGL(k_adj_unsweep_correct<W>, dim3(gb), dim3(256), 0, s, a, it);
