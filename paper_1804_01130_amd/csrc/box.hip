@@ -280,13 +280,81 @@ __device__ __forceinline__ void gather(const DevMesh &m, const double *x, const 
     }
 }
 
+// The weighted sum of two vertices' velocities (components along the coordinate axes ax): the stencils of both
+// first, then four cells of each at a time with all their components in flight.  Cell by cell the loads waited
+// for each other; with its own registers (one wave per SIMD) the kernel went from 29.5 to 21.2 us on an outer
+// iteration's 75x37x41 box and from 45.5 to 34.0 on 200x96x96, with two waves (spilled) 22.8 and 39.4.
+template <int kN>
+__device__ __forceinline__ void gather_velocity(const SurfArgs &A, const int (&ax)[3], const int32_t (&k)[2],
+                                                const double (&w)[2], double (&us)[3]) {
+    const size_t nc = A.m.n_cells;
+    const double *U[3], *U1[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        U[i] = A.U + ax[i] * nc;
+        U1[i] = A.U1 + ax[i] * nc;
+    }
+    int32_t c[2][kN];
+    double sw[2][kN], uv[2][3];
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+        const int4 *cp = reinterpret_cast<const int4 *>(A.m.sten_cell + (size_t)kN * k[v]);
+        const double2 *wp = reinterpret_cast<const double2 *>(A.m.sten_w + (size_t)kN * k[v]);
+#pragma unroll
+        for (int j = 0; j < kN; j += 4) {
+            const int4 q = cp[j / 4];
+            c[v][j] = q.x; c[v][j + 1] = q.y; c[v][j + 2] = q.z; c[v][j + 3] = q.w;
+        }
+#pragma unroll
+        for (int j = 0; j < kN; j += 2) {
+            const double2 q = wp[j / 2];
+            sw[v][j] = q.x; sw[v][j + 1] = q.y;
+        }
+#pragma unroll
+        for (int i = 0; i < 3; ++i) uv[v][i] = 0.0;
+    }
+#pragma unroll
+    for (int j0 = 0; j0 < kN; j0 += 4) {
+        double u[2][4][3];
+#pragma unroll
+        for (int v = 0; v < 2; ++v)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int i = 0; i < 3; ++i) u[v][j][i] = U[i][c[v][j0 + j]];
+        if (A.U1) {
+            double u1[2][4][3];
+#pragma unroll
+            for (int v = 0; v < 2; ++v)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) u1[v][j][i] = U1[i][c[v][j0 + j]];
+#pragma unroll
+            for (int v = 0; v < 2; ++v)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) u[v][j][i] = 0.5 * (u[v][j][i] + u1[v][j][i]);
+        }
+#pragma unroll
+        for (int v = 0; v < 2; ++v)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int i = 0; i < 3; ++i) uv[v][i] = fma(sw[v][j0 + j], u[v][j][i], uv[v][i]);
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) us[i] = fma(w[1], uv[1][i], w[0] * uv[0][i]);
+}
+
 // Work-groups of one wave: the list's waves then spread evenly over the CUs (1116 interface cells of a slab
 // 17.0 us against 19.7 with 256 threads, 45k of a box 28.2 against 30.0).
 constexpr int kBlock = 64, kGroups = kBlock / 2;  // threads and interface cells of a work-group
 
 // kInterp: U_S by cell-point interpolation (us_mode 1) instead of U_P.
 template <bool kInterp>
-__global__ void __launch_bounds__(kBlock, 2) k_surface_box(SurfArgs A) {
+__global__ void __launch_bounds__(kBlock, kInterp ? 1 : 2) k_surface_box(SurfArgs A) {
     const DevMesh &m = A.m;
     const int r = threadIdx.x & 1;
     const int n = min(A.counters[kCntSurf], A.cap);
@@ -677,27 +745,16 @@ __global__ void __launch_bounds__(kBlock, 2) k_surface_box(SurfArgs A) {
                 const double ya = pick(fa), yb = pick(fb), yc = pick(fc);
                 const double t = 2.0 * fabs(ya), e = 2.0 * fabs(yb);
                 const double end = 0.5 * (e + (r ? 2.0 * yc : -2.0 * yc));
-                double us[3] = {0.0, 0.0, 0.0};
+                double w[2], us[3];
+                int32_t k[2];
 #pragma unroll
                 for (int v = 0; v < 2; ++v) {
                     const int b = ((ya >= 0.0 ? 1 : 0) << fa) | (v << fb) | (r << fc);
-                    const double w = 0.25 * (t - e) + (v == (yb >= 0.0 ? 1 : 0) ? end : 0.0);
-                    const int k = m.cpt[8 * (size_t)c + ((kBoxCanon >> (4 * b)) & 7u)];
-                    double uv[3] = {0.0, 0.0, 0.0};
-#pragma unroll 4
-                    for (int j = 0; j < m.sten_n; ++j) {
-                        const size_t e = (size_t)m.sten_n * k + j;
-                        const int32_t sc = m.sten_cell[e];
-                        const double sw = m.sten_w[e];
-#pragma unroll
-                        for (int i = 0; i < 3; ++i) {
-                            const size_t at = ax[i] * nc + sc;
-                            uv[i] = fma(sw, A.U1 ? 0.5 * (A.U[at] + A.U1[at]) : A.U[at], uv[i]);
-                        }
-                    }
-#pragma unroll
-                    for (int i = 0; i < 3; ++i) us[i] = fma(w, uv[i], us[i]);
+                    w[v] = 0.25 * (t - e) + (v == (yb >= 0.0 ? 1 : 0) ? end : 0.0);
+                    k[v] = m.cpt[8 * (size_t)c + ((kBoxCanon >> (4 * b)) & 7u)];
                 }
+                if (m.sten_n == 4) gather_velocity<4>(A, ax, k, w, us);
+                else gather_velocity<8>(A, ax, k, w, us);
 #pragma unroll
                 for (int i = 0; i < 3; ++i) U[i] = fma(1.0 - t, U[i], us[i] + swap1(us[i]));
             }
