@@ -34,8 +34,9 @@ HBM_PEAK_GBS = 8000.0
 FP64_VECTOR_TFLOPS = 78.6
 # sources of the kernels that the profiled commands launch (their meshes are hexahedra only, so the
 # polyhedron kernel of big.hip is not among them)
-KERNEL_SRCS = [os.path.join(ROOT, "paper_1804_01130_amd", "csrc", n) for n in ("kernels.hip", "device_common.h",
-                                                                                "internal.h", "gfm.hip", "relax.hip")]
+KERNEL_SRCS = [os.path.join(ROOT, "paper_1804_01130_amd", "csrc", n) for n in ("kernels.hip", "box.hip",
+                                                                                "device_common.h", "internal.h",
+                                                                                "gfm.hip", "relax.hip")]
 PROFILES = os.path.join(ROOT, "profiles")
 # FP64 operations credited per interface cell for vertex interpolation, the isovalue search, the
 # isoface and the swept-face integrals (a fixed per-unit figure, independent of the iteration
@@ -43,7 +44,7 @@ PROFILES = os.path.join(ROOT, "profiles")
 FLOP_PER_SURFACE_CELL = 11000.0
 COPY_N = 1 << 27  # doubles moved by the calibration copy (1 GiB read, 1 GiB written)
 KERNEL_KEYS = {"k_find_surface": "find_surface", "k_surface": "surface", "k_update": "update",
-               "k_bound_sweep": "bound_sweep", "k_bound_end": "bound_end",
+               "k_bound_sweep": "bound_sweep", "k_bound_group": "bound_group", "k_bound_end": "bound_end",
                "k_gfm_faces": "gfm_faces", "k_relax_blend": "relax_blend", "k_stats": "stats"}
 # the commands whose rocprofv3 output --summarize-profiles reads: a window of 20 steps after 5
 # warm-up steps, with only the step's own kernels (the summaries record the window's interface-cell
@@ -255,7 +256,7 @@ def summarize_ensemble_profile():
     t0 = finds[-steps]
     by = {}
     for k, r in keys:
-        if k in ("find_surface", "surface", "surface_big", "update", "bound_sweep", "bound_end") and \
+        if k in ("find_surface", "surface", "surface_big", "update", "bound_sweep", "bound_group", "bound_end") and \
                 int(r["Start_Timestamp"]) >= t0:
             by.setdefault(k, []).append((int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) * 1e-3)
     lines = [f"# rocprofv3 kernel trace, workload {ens['workload']}: the timed batched run",
@@ -266,7 +267,7 @@ def summarize_ensemble_profile():
              f"{ens['tuned_config']}",
              "# kernel | dispatches | per step | mean us | min us | max us"]
     tot = 0.0
-    for k in ("find_surface", "surface", "surface_big", "update", "bound_sweep", "bound_end"):
+    for k in ("find_surface", "surface", "surface_big", "update", "bound_sweep", "bound_group", "bound_end"):
         if k not in by:
             continue
         d = by[k]
@@ -301,7 +302,7 @@ def summarize_profiles(workload):
     by = {}
     for r in sorted(trace, key=lambda r: int(r["Start_Timestamp"])):
         k = _kernel_key(r["Kernel_Name"])
-        if k in ("find_surface", "surface", "update", "bound_sweep", "bound_end"):
+        if k in ("find_surface", "surface", "update", "bound_sweep", "bound_group", "bound_end"):
             by.setdefault(k, []).append((int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) * 1e-3)
     lines = [f"# rocprofv3 kernel trace, workload {workload}: the window the benchmark line times",
              f"# command (repository root): {cmds['stats']}",
@@ -358,7 +359,7 @@ def summarize_profiles(workload):
              f"kernel_source_sha: {shas.pop()}",
              f"scale_fetch: {sf:.6f}",
              f"scale_write: {sw:.6f}"]
-    for k in ("find_surface", "surface", "update", "bound_sweep", "bound_end", "gfm_faces", "relax_blend"):
+    for k in ("find_surface", "surface", "update", "bound_sweep", "bound_group", "bound_end", "gfm_faces", "relax_blend"):
         if k not in fetch or k not in write:
             continue
         fk = float(np.mean(fetch[k]))
@@ -384,7 +385,7 @@ def summarize_profiles(workload):
                  "# per-wave figures divide by SQ_WAVES; SQ_BUSY_CYCLES is summed over the shader engines",
                  "# kernel | dispatches | waves | VALU/wave | SALU/wave | VMEM_RD/wave | LDS/wave | WAVE_CYCLES/wave | "
                  "VALU instructions"]
-        for k in ("surface", "update", "find_surface", "bound_sweep", "bound_end", "gfm_faces", "relax_blend"):
+        for k in ("surface", "update", "find_surface", "bound_sweep", "bound_group", "bound_end", "gfm_faces", "relax_blend"):
             if k not in per:
                 continue
             mean = {n: sum(v.values()) / max(len(v), 1) for n, v in per[k].items()}

@@ -1129,9 +1129,10 @@ struct BoundArgs {
 // so it alone writes that face's correction and its running dV) and marks the cells it touches;
 // (B) every touched cell applies the corrections of its faces in ascending face order.  Phase A
 // of a cell needs only its own new alpha and its own outflow faces, so a cell still out of bounds
-// after phase B of sweep s runs phase A of sweep s+1 at once: one kernel per sweep (phase A of
-// sweep 0 runs inside the update).  Touched lists and marks alternate between two banks, counter
-// slots rotate over four.  List order never affects a result.
+// after phase B of sweep s runs phase A of sweep s+1 at once: one pass per sweep (phase A of sweep
+// 0 runs inside the update), a launch or a turn of k_bound_group.  Touched lists and marks
+// alternate between two banks, counter slots rotate over four.  List order never affects a result.
+
 // Where a sweep finds and leaves its counts: the counter slots in memory, or a work-group's own.
 struct BoundCounts {
     int stale, touched, faces;  // sweep it-1's corrections; cells touched in sweep it; faces marked so far
