@@ -323,7 +323,8 @@ def summarize_profiles(workload):
         tf = FLOP_PER_SURFACE_CELL * n_s / (means["surface"] * 1e-6) / 1e12
         lines.append(f"# k_surface: {FLOP_PER_SURFACE_CELL:.0f} flop x {n_s:.0f} interface cells / {means['surface']:.2f} us"
                      f" = {tf:.3f} TFLOP/s = {tf / FP64_VECTOR_TFLOPS:.4f} of the {FP64_VECTOR_TFLOPS} TFLOP/s FP64 peak"
-                     f" (the line reported {run['roofline']['frac']:.4f} from its own events)")
+                     + (f" (the line reported {run['roofline']['frac']:.4f} from its own events)"
+                        if run['roofline']['kernel'] == "surface" else ""))
     lines.append("# whole run (rocprofv3 --stats): name | calls | total ms | average us | min us | max us | share %")
     for r in csv.DictReader(open(_find("gpurun_out/prof_stats", "kernel_stats.csv"))):
         lines.append(f"{r['Name'][:60]} | {r['Calls']} | {float(r['TotalDurationNs']) / 1e6:.3f} | "
