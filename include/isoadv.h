@@ -79,13 +79,16 @@ typedef struct {
     int32_t n_bound_iter;   /* Jacobi redistribution sweeps (default 3) */
     int32_t clip;           /* chop alpha to [0,1] after redistribution (default 1) */
     int32_t check_inputs;   /* validate inputs on the host before each step (syncs; default 0) */
-    int32_t block_cells;    /* threads per block of the per-cell kernels, up to 1024 (0 = 256) */
-    int32_t surface_blocks; /* work-groups of the interface-cell kernel, which loops over the list
-                               (0 = up to 2048, from the list capacity); at most 65535 */
+    int32_t block_cells;    /* threads per block of the per-cell kernels, up to 1024 (0 = 256); the
+                               update of cells with more than eight flux slots takes 256 at most */
+    int32_t surface_blocks; /* work-groups of the interface-cell kernels, which loop over the list, in
+                               units of 256 threads (0 = up to 2048, from the list capacity); at
+                               most 65535 */
     int32_t max_surface;    /* capacity of the interface-cell list (0 = n_cells) */
     int32_t surface_waves;  /* register budget of the interface-cell kernel in waves per SIMD:
-                               1, 2, 3 or 4 (0 = 2) */
-    int32_t bound_blocks;   /* work-groups of the bounding sweeps (0 = 512); at most 65535.
+                               1, 2, 3 or 4 (0 = 2); the kernel of rectangular hexahedra has its own */
+    int32_t bound_blocks;   /* work-groups of the bounding sweeps that run on the whole grid (0 = 512);
+                               at most 65535.
                                Results are bitwise the same for every choice of the launch shapes
                                block_cells, surface_blocks, surface_waves and bound_blocks. */
     int32_t us_mode;        /* isoface velocity U_S (Section 3.2 interpolates the cell velocity to
