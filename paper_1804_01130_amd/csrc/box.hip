@@ -423,7 +423,10 @@ __global__ void __launch_bounds__(kBlock, kInterp ? 1 : 2) k_surface_box(SurfArg
         exch(0, 4); exch(1, 5); exch(2, 6); exch(3, 7);
         exch(2, 4); exch(3, 5);
         exch(1, 2); exch(3, 4); exch(5, 6);
-        bool recon = s[7] - s[0] > A.flat_tol;
+        // a vertex value that is no number, or infinite, leaves no isoface (and the bulk flux), as in
+        // k_surface; the clamps below would make a cut of it, and the sort has dropped it
+        const double mag = fabs(cell.a[0]) + fabs(cell.a[1]) + fabs(cell.a[2]) + fabs(cell.a[4]);
+        bool recon = s[7] - s[0] > A.flat_tol && mag + swap1(mag) < INFINITY;
         double iso = 0.0, un = 0.0;
         int rounds = 0;
         double S[3] = {0.0, 0.0, 0.0}, N[3] = {0.0, 0.0, 0.0};  // isoface centre (local) and normal per edge direction
@@ -782,9 +785,12 @@ __global__ void __launch_bounds__(kBlock, kInterp ? 1 : 2) k_surface_box(SurfArg
         }
         // the lane's outflow faces
         const double dtc = cell_dt(m, A.dt_dom, A.dt, c);
-        // a plane at rest counts as one that moves by less than any distance of its cell
+        // a plane at rest counts as one that moves by less than any distance of its cell, one of infinite
+        // speed as one that moves by more, and so, forwards, one whose speed is no number (as in k_surface)
         double ud = un * dtc;
         if (fabs(ud) < 1e-200) ud = 1e-200;
+        if (!(ud < 1e200)) ud = 1e200;
+        if (ud < -1e200) ud = -1e200;
         const double iud = recip(ud);
         double nl[3], d0 = 0.0;  // change of the distance along each local coordinate; distance at the origin
 #pragma unroll
