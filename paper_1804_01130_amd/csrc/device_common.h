@@ -200,6 +200,27 @@ __device__ __forceinline__ int3 wave_append3(int3 count, int32_t *cx, int32_t *c
                      __shfl(b.z, top, 64) + (int)(before >> 40));
 }
 
+// Whether this work-group is the last of its launch to come here, all of it; `count`, zero before, is left
+// zero.  The last one then sees what every group stored before it came.  (No group waits for another.)
+__device__ __forceinline__ bool last_group(int32_t *count) {
+    __shared__ bool last;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __threadfence();
+        last = atomicAdd(count, 1) == (int)gridDim.x - 1;
+        if (last) {
+            *count = 0;
+            __threadfence();
+        }
+    }
+    __syncthreads();
+    return last;
+}
+// A word that another group of the launch may have changed.
+__device__ __forceinline__ int32_t load_shared(const int32_t *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 }  // namespace
 // ------------------------------------------------------------------------------------------ sweep
 // Integral over s in [0, dt] of the submerged fraction of a triangle with signed distances

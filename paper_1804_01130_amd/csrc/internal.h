@@ -150,6 +150,7 @@ enum : int {
     kCntActive0 = 6,    // n_bound_active of the last step
     kCntFaces = 7,      // flist length
     kCntBound = 16,     // [16, 24): four rotating slots of per-sweep bounding counters
+    kCntGroups = 24,    // work-groups of a bounding launch that are done, zero between launches
     kCntNum = 32
 };
 
@@ -182,9 +183,11 @@ struct Params {
     double root_tol;  // isovalue search stops at |V_sub/V - alpha| <= root_tol (0: to round-off)
 };
 
-// Bounding sweeps in one work-group: up to this many cells all of them, and its threads for W flux slots
-// (k_bound_group has the reasons).
+// Bounding sweeps (k_bound_group has the reasons): cells of a mesh above which the first sweep is a launch of
+// its own, touched cells that one work-group walks alone, the work-groups for more, and their threads for W flux
+// slots.
 constexpr int kBoundGroupCells = 1 << 17;
+constexpr int kBoundAlone = 512, kBoundGroups = 32;
 constexpr int bound_threads(int W) { return W > 8 ? 512 : 1024; }
 
 // Adjoint workspace (device pointers; allocated by a plan on its first adjoint step).  S = number of

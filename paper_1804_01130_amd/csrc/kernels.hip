@@ -1160,11 +1160,18 @@ __device__ __forceinline__ void bound_sweep(const BoundArgs &A, int it, int b0, 
     const int nT = C.touched;
     if (last) {
         // no phase A in the last sweep reads the face marks, and the list of marked faces is
-        // complete: clear them here, over the whole grid, rather than at the end
-        for (int i = t0; i < C.faces; i += stride) A.w.fmark[A.w.flist[i]] = 0;
+        // complete: clear them here rather than at the end
+        int i = t0;
+        for (; C.faces - i > 7 * stride; i += 8 * stride) {  // a long list's loads eight at a time
+            int32_t f[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) f[k] = A.w.flist[i + k * stride];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) A.w.fmark[f[k]] = 0;
+        }
+        for (; i < C.faces; i += stride) A.w.fmark[A.w.flist[i]] = 0;
     }
-    const int nloop = (nT + (int)blockDim.x - 1) / (int)blockDim.x * (int)blockDim.x;  // whole work-groups iterate together
-    for (int i0 = b0; i0 < nloop; i0 += stride) {
+    for (int i0 = b0; i0 < nT; i0 += stride) {  // whole waves iterate together
         const int i = i0 + threadIdx.x;
         bool again = false;
         int32_t Q = 0;
@@ -1322,36 +1329,55 @@ __global__ void __launch_bounds__(1024) k_bound_end(BoundArgs A) {
     bound_end(A, A.n_iter > 0 ? bound_slot(A.w.counters, A.n_iter - 1)[kSlotDelta] : 0);
 }
 
-// The sweeps from `first` on and the end of the step in one work-group, its counts in LDS.  What a
-// sweep costs is its launch and one chain of dependent loads, as long as its list is no longer than
-// the work-group; a long list wants the whole chip, and the first one is the longest.  So up to
-// kBoundGroupCells every sweep runs here, above it the first sweep runs on the grid, and all sweeps of
-// an ensemble, whose lists are those of its members together.
-// Whole steps in us, all sweeps on the grid / first on the grid / none:
-//   calm slab 384x96 34.8 / - / 30.2, 1024x256 40.7 / 38.3 / 35.6, box 151x75x85 68.1 / 63.8 / 61.1
-//   violent box (cells out of bounds) 64x32x32 (100) 46.0 / 43.8 / 41.9, 96x48x48 (300)
-//   58.7 / 55.9 / 60.3, 128x64x64 (500) 74.8 / 72.1 / 85.3, 256x128x128 (1200) 169.4 / 169.5 / -;
-//   calm 250x128x128 124.5 / 121.0 / 120.4; 5 steps of an ensemble of 64 tanks 856 / 895 / -
-// With a second sweep on the grid, 66.8 on 151x75x85 and 73.6 on 128x64x64.
+// The sweeps from `first` on and the end of the step in one launch.  What a sweep costs is its launch and one
+// chain of dependent loads, as long as its list is short: up to kBoundAlone touched cells one work-group walks
+// it alone, its counts in LDS, and the others leave at once.  A longer list wants more of the chip: all
+// kBoundGroups groups walk sweep `first`, in strides that give each a part, and the last to end (nobody waits)
+// goes on alone, as the sweeps after it have a tenth of its cells or fewer.  What it has to see of the
+// others' stores costs some 5 us, a launch 1.5; so above kBoundGroupCells, where the first list is nearly always
+// long, the first sweep is a launch of its own on the whole grid, and `first` is the second.  The sweeps of an
+// ensemble all are, as their lists are those of its members together.
+// Bounding stage in us (events), all sweeps on the grid / by one group whatever the length / this:
+//   calm slab 384x96 11.5 / 6.3 / 6.4, box 64x32x32 11.5 / 6.5 / 6.5, slab 1024x256 12.4 / 10.9 / 11.0
+//   random fields (cells out of bounds) on 64x32x32: (107) 13.2 / 10.0 / 10.5, (338) 21.0 / 20.9 / 17.0,
+//   (737) 21.2 / 33 / 18.7; on 64x64x32: (257) 20.4 / 18.8 / 16.2, (979) 21.8 / 43.6 / 20.0;
+//   on 128x64x64 (5582) 24.8 / 35.0 / 34;
+//   100 steps of the violent 256x128x128 box (440 to 2848) 31.6 on average and 41 at most / 27.8 and 134 /
+//   27 and 64.
+// By kBoundAlone 256, 512 or 1024 for 64x32x32 (338): 17.3, 17.0, 21.4; by 16, 32 or 128 groups for calm
+// lists, which then leave at once: +0.1, +0.2, +1 us.
 template <int W, bool kAvg>
 __global__ void __launch_bounds__(bound_threads(W)) k_bound_group(BoundArgs A, int first) {
     __shared__ int32_t cnt[2][4], faces;
     int32_t *counters = A.w.counters;
-    const int tid = threadIdx.x;
-    if (tid < 2) cnt[first & 1][tid] = bound_slot(counters, first)[tid];
-    if (tid == 2) faces = counters[kCntFaces];
-    int stale = first > 0 ? bound_slot(counters, first - 1)[kSlotDelta] : 0;
-    for (int it = first; it < A.n_iter; ++it) {
+    const int tid = threadIdx.x, bd = blockDim.x;
+    int it = first, stale = first > 0 ? bound_slot(counters, first - 1)[kSlotDelta] : 0;
+    const int nT = bound_slot(counters, first)[kSlotTouched];
+    if (__builtin_expect(nT > kBoundAlone && gridDim.x > 1, 0)) {
+        int32_t *next = bound_slot(counters, first + 1);
+        const int nd = bound_slot(counters, first)[kSlotDelta], width = min((nT / (int)gridDim.x + 64) & ~63, bd);
+        if (tid < width)
+            bound_sweep<W, kAvg>(A, first, blockIdx.x * width, gridDim.x * width,
+                                 {stale, nT, counters[kCntFaces], &next[kSlotDelta], &next[kSlotTouched], &counters[kCntFaces]});
+        if (!last_group(&counters[kCntGroups])) return;
+        ++it;
+        stale = nd;
+    } else if (blockIdx.x != 0) {
+        return;
+    }
+    if (tid < 2) cnt[it & 1][tid] = load_shared(&bound_slot(counters, it)[tid]);
+    if (tid == 2) faces = load_shared(&counters[kCntFaces]);
+    for (; it < A.n_iter; ++it) {
         int32_t *now = cnt[it & 1], *next = cnt[(it + 1) & 1];
         if (tid < 2) next[tid] = 0;
         __syncthreads();
         const int nT = now[kSlotTouched], nd = now[kSlotDelta], nF = faces;
         __syncthreads();
-        bound_sweep<W, kAvg>(A, it, 0, blockDim.x, {stale, nT, nF, &next[kSlotDelta], &next[kSlotTouched], &faces});
+        bound_sweep<W, kAvg>(A, it, 0, bd, {stale, nT, nF, &next[kSlotDelta], &next[kSlotTouched], &faces});
         stale = nd;
         __syncthreads();
     }
-    if (tid == 0) counters[kCntFaces] = faces;
+    if (tid == 2) counters[kCntFaces] = faces;
     bound_end(A, stale);
 }
 
@@ -1424,12 +1450,13 @@ void launch_wide(const DevMesh &m, const UpdArgs &ua, const BoundArgs &ba, const
     if (m.n_dom > 0) hipLaunchKernelGGL((k_update<W, kAvg, true>), dim3(gc), dim3(bc), 0, s, ua);
     else hipLaunchKernelGGL((k_update<W, kAvg, false>), dim3(gc), dim3(bc), 0, s, ua);
     if (ev) (void)hipEventRecord(ev[3], s);
-    // sweeps over the whole grid
+    // sweeps over the whole grid (k_bound_group has the reasons)
     const int grid = std::min(ba.n_iter, m.n_cells <= kBoundGroupCells ? 0 : m.n_dom > 0 ? ba.n_iter : 1);
     for (int it = 0; it < grid; ++it)
         hipLaunchKernelGGL((k_bound_sweep<W, kAvg>), dim3(cfg.bound_blocks), dim3(256), 0, s, ba, it);
     if (grid < ba.n_iter) {
-        hipLaunchKernelGGL((k_bound_group<W, kAvg>), dim3(1), dim3(bound_threads(W)), 0, s, ba, grid);
+        const int bt = bound_threads(W), gb = std::min(kBoundGroups, (m.n_cells + bt - 1) / bt);
+        hipLaunchKernelGGL((k_bound_group<W, kAvg>), dim3(gb), dim3(bt), 0, s, ba, grid);
         return;
     }
     hipLaunchKernelGGL(k_bound_end, dim3(1), dim3(1024), 0, s, ba);
