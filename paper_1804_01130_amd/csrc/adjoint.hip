@@ -343,17 +343,17 @@ __device__ __forceinline__ int adj_count(const AdjArgs &A, int i) {
 
 // Phase B of sweep s: every touched cell applies its faces' corrections in ascending face order
 // (round-off chop; clamp on the last sweep); a cell still out of bounds runs phase A of sweep s+1.
+// Over the cells b0 + threadIdx.x, and so on every `stride`.
 template <int W>
 __device__ __forceinline__ void adj_sweep(const AdjArgs &A, int s, int b0, int stride) {
     const int n = A.m.n_cells, nf = A.m.n_faces;
     const DevMesh &m = A.m;
     const AdjWork &w = A.w;
-    const int t0 = b0 + threadIdx.x;
     const bool last = s == A.n_iter - 1;
     if (s >= 1) {  // sweep s-1's corrections were read by the previous kernel: clear them
         const int np = adj_count(A, kAdjL + s - 1);
         double *stale = w.delta + (size_t)((s - 1) % 3) * nf;
-        for (int i = t0; i < np; i += stride) {
+        for (int i = b0 + threadIdx.x; i < np; i += stride) {
             const int32_t P = w.list[(size_t)(s - 1) * n + i];
             const uint64_t flags = w.tflag[(size_t)(s - 1) * n + i];
 #pragma unroll
@@ -368,9 +368,8 @@ __device__ __forceinline__ void adj_sweep(const AdjArgs &A, int s, int b0, int s
     const int32_t *T = w.tlist + (size_t)s * n;
     int32_t *mark = w.cmark + (size_t)(s & 1) * n;
     int32_t *mark_next = w.cmark + (size_t)((s + 1) & 1) * n;
-    const int nT = adj_count(A, kAdjT + s), bd = blockDim.x;
-    const int nloop = (nT + bd - 1) / bd * bd;  // whole work-groups iterate together
-    for (int i0 = b0; i0 < nloop; i0 += stride) {
+    const int nT = adj_count(A, kAdjT + s);
+    for (int i0 = b0; i0 < nT; i0 += stride) {  // whole waves iterate together
         const int i = i0 + threadIdx.x;
         bool again = false;
         int32_t Q = 0;
@@ -536,10 +535,15 @@ __device__ __forceinline__ void adj_unsweep_correct(const AdjArgs &A, int s, int
     }
 }
 
-// The sweeps on the grid, and all from `first` on, forwards and back, in one work-group: their lists are
-// short, and what they cost is their launches (see k_bound_group of the step, whose lists they are).
+// The sweeps on the grid, and all from `first` on, forwards and back, in one launch, as in k_bound_group of the
+// step (whose lists these are): a short list costs its launch and a chain of loads, so one work-group walks it
+// alone; a long first list, forwards, all do (the way back stays with the last of them: its lists are the cells
+// out of bounds, a sixth of those touched).  From k_adj_prep to k_adj_faces in us, nine launches / one group
+// whatever the length / this: random fields on 64x32x32 (737 cells out of bounds) 65 / 78 / 65, on 64x64x32
+// (979) 67 / 106 / 86, on 192x96x96 the violent start (1148) 109 / 159 / 132, after 20 steps on 64x64x32 (132)
+// 102 / 26 / 27.
 // A traced step and adjoint of 128x64x64 cells and the gradient of five 256x128 slab steps: nine launches
-// 252 and 845 us, with this (and the gathers of k_adj_faces straight-line) 221 and 750, with the loads of
+// 252 and 845 us, one group (and the gathers of k_adj_faces straight-line) 221 and 750, with the loads of
 // a sweep's cell batched, none behind a branch, 205 and 660 (this kernel on the slab 18.3 -> 11.9; on the box
 // 18.0, with 1024 threads and their 128 registers 27.5).
 template <int W>
@@ -557,8 +561,17 @@ __global__ void __launch_bounds__(256) k_adj_unsweep_correct(AdjArgs A, int s) {
 constexpr int adj_group_threads(int W) { return W > 8 ? 256 : W > 4 ? 512 : 1024; }  // (its registers fit)
 template <int W>
 __global__ void __launch_bounds__(adj_group_threads(W)) k_adj_group(AdjArgs A, int first) {
-    const int t = threadIdx.x, nt = blockDim.x;
-    for (int s = first; s < A.n_iter; ++s) {
+    const int t = threadIdx.x, nt = blockDim.x, nT = adj_count(A, kAdjT + first);
+    int s0 = first;
+    if (__builtin_expect(nT > kBoundAlone && gridDim.x > 1, 0)) {
+        const int width = min((nT / (int)gridDim.x + 64) & ~63, nt);
+        if (t < width) adj_sweep<W>(A, first, blockIdx.x * width, gridDim.x * width);
+        if (!last_group(&A.w.counters[kAdjGroups])) return;
+        ++s0;
+    } else if (blockIdx.x != 0) {
+        return;
+    }
+    for (int s = s0; s < A.n_iter; ++s) {
         adj_sweep<W>(A, s, 0, nt);
         __syncthreads();
     }
@@ -1440,7 +1453,9 @@ hipError_t launch_adj_w(const AdjArgs &a, hipStream_t s) {
     hipLaunchKernelGGL(k_adj_prep<W>, dim3(g), dim3(256), 0, s, a);
     const int grid = std::min(a.n_iter, n <= kBoundGroupCells ? 0 : 1);  // sweeps over the whole grid
     for (int it = 0; it < grid; ++it) hipLaunchKernelGGL(k_adj_sweep<W>, dim3(gb), dim3(256), 0, s, a, it);
-    if (grid < a.n_iter) hipLaunchKernelGGL(k_adj_group<W>, dim3(1), dim3(adj_group_threads(W)), 0, s, a, grid);
+    const int gt = adj_group_threads(W);
+    if (grid < a.n_iter)
+        hipLaunchKernelGGL(k_adj_group<W>, dim3(std::min(kBoundGroups, (n + gt - 1) / gt)), dim3(gt), 0, s, a, grid);
     for (int it = grid - 1; it >= 0; --it) {
         hipLaunchKernelGGL(k_adj_unsweep_apply<W>, dim3(gb), dim3(256), 0, s, a, it);
         hipLaunchKernelGGL(k_adj_unsweep_correct<W>, dim3(gb), dim3(256), 0, s, a, it);

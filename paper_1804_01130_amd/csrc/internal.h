@@ -193,9 +193,9 @@ constexpr int bound_threads(int W) { return W > 8 ? 512 : 1024; }
 // Adjoint workspace (device pointers; allocated by a plan on its first adjoint step).  S = number of
 // bounding sweeps (at least 1), nc cells, nf faces.
 // adjoint counters: the interface cells, the polyhedra's (cell, direction) pairs to differentiate
-// along, then per sweep s the length of its list of
+// along, the work-groups of a bounding launch that are done (zero between launches), then per sweep s the length of its list of
 // cells out of bounds (kAdjL + s) and of the cells its corrections touch (kAdjT + s)
-enum : int { kAdjCells = 2, kAdjDirsBig = 3, kAdjGBig = 68, kAdjL = 8, kAdjT = 40, kAdjNum = 72, kAdjMaxSweeps = 31, kAdjG = 9,
+enum : int { kAdjCells = 2, kAdjDirsBig = 3, kAdjGroups = 4, kAdjGBig = 68, kAdjL = 8, kAdjT = 40, kAdjNum = 72, kAdjMaxSweeps = 31, kAdjG = 9,
              kAdjBoundBlocks = 512 };
 struct AdjWork {
     int32_t *counters = nullptr;  // [kAdjNum]
