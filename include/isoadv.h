@@ -331,8 +331,8 @@ iso_status iso_batch_config(const iso_batch *batch, int32_t *cfg);
 iso_status iso_batch_set_config(iso_batch *batch, const int32_t *cfg);
 /* Autotuner: times n_trial steps of every candidate launch shape (coordinate search over the
  * interface kernel's register budget and work-group count, the per-cell block size and the
- * bounding grid) from state alpha with the fields phi, U of one step (alpha is not modified)
- * and keeps the fastest.  cache_path (nullable): text file of earlier choices keyed by the
+ * bounding grid; not over a shape that no kernel of the ensemble reads, which stays as it is) from
+ * state alpha with the fields phi, U of one step (alpha is not modified) and keeps the fastest.  cache_path (nullable): text file of earlier choices keyed by the
  * ensemble's layout; a match skips the trials, a new choice is appended.  best_ms (nullable): the
  * chosen shape's ms per step.  Synchronous. */
 iso_status iso_batch_tune(iso_batch *batch, const double *alpha, const double *phi, const double *U, const double *dt,

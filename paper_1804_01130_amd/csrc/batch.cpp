@@ -522,7 +522,11 @@ iso_status iso_batch_tune(iso_batch *b, const double *alpha, const double *phi, 
         *ms = f / n_trial;
         return e;
     };
-    // coordinate search: interface-kernel shape first, then the per-cell block, then bounding
+    // coordinate search: interface-kernel shape first, then the per-cell block, then bounding; not over
+    // shapes that no kernel of this ensemble reads (the register budget where every cell is a rectangular
+    // hexahedron or a general polyhedron, the grid of the sweeps where one launch runs them)
+    const DevMesh &dm = b->u->dev;
+    const bool budget = dm.box != 1 && !dm.all_big, grid = N > kBoundGroupCells && b->plan->opt.n_bound_iter > 0;
     LaunchCfg best = b->cfg;
     double best_t = 0;
     hipError_t e = trial(best, &best_t);
@@ -532,9 +536,9 @@ iso_status iso_batch_tune(iso_batch *b, const double *alpha, const double *phi, 
     const int bblocks[] = {256, 512, 1024};
     for (int sw : waves)
         for (int sb : sblocks) {
-            if (e != hipSuccess) break;
+            if (e != hipSuccess || (!budget && sw != waves[0])) break;
             LaunchCfg c = best;
-            c.surface_waves = sw;
+            if (budget) c.surface_waves = sw;
             c.surface_blocks = sb;
             double t;
             e = trial(c, &t);
@@ -549,7 +553,7 @@ iso_status iso_batch_tune(iso_batch *b, const double *alpha, const double *phi, 
         if (e == hipSuccess && t < best_t) { best_t = t; best = c; }
     }
     for (int bb : bblocks) {
-        if (e != hipSuccess) break;
+        if (e != hipSuccess || !grid) break;
         LaunchCfg c = best;
         c.bound_blocks = bb;
         double t;
