@@ -131,9 +131,9 @@ struct DevWork {
     double *sbnd = nullptr;        // [n_cells] volume through the cell's boundary faces (statistics only)
     double *sclip = nullptr;       // [n_cells] volume the chops added to the cell (statistics only)
     int32_t cap = 0;
-    // meshes with general polyhedra: a second stream (default priority) for their interface
-    // kernel, forked once the interface list is built and joined before the update, so that it
-    // runs beside the eight-lane kernel
+    // meshes with general polyhedra, and ensembles of rectangular hexahedra and other cells: a second
+    // stream (default priority) for their interface kernel, forked once the interface list is built and
+    // joined before the update, so that it runs beside the eight-lane kernel
     hipStream_t side = nullptr;
     hipEvent_t fork = nullptr, join = nullptr;
 };

@@ -977,9 +977,11 @@ iso_status iso_plan_create(const iso_mesh *mesh, const iso_options *opt, void *s
         iso_plan_destroy(p);
         return fail(ISO_ENOMEM, "plan workspace allocation failed");
     }
-    if (mesh->dev.cbig && !mesh->dev.all_big && (hipStreamCreateWithFlags(&w.side, hipStreamNonBlocking) != hipSuccess ||
-                           hipEventCreateWithFlags(&w.fork, hipEventDisableTiming) != hipSuccess ||
-                           hipEventCreateWithFlags(&w.join, hipEventDisableTiming) != hipSuccess)) {
+    const DevMesh &dm = mesh->dev;
+    const bool beside = (dm.cbig && !dm.all_big) || (dm.box == 2 && !dm.cbig);  // two interface kernels side by side
+    if (beside && (hipStreamCreateWithFlags(&w.side, hipStreamNonBlocking) != hipSuccess ||
+                   hipEventCreateWithFlags(&w.fork, hipEventDisableTiming) != hipSuccess ||
+                   hipEventCreateWithFlags(&w.join, hipEventDisableTiming) != hipSuccess)) {
         iso_plan_destroy(p);
         return fail(ISO_EDEVICE, "side stream creation failed");
     }
