@@ -39,9 +39,10 @@ KERNEL_SRCS = [os.path.join(ROOT, "paper_1804_01130_amd", "csrc", n) for n in ("
                                                                                 "gfm.hip", "relax.hip")]
 PROFILES = os.path.join(ROOT, "profiles")
 # FP64 operations credited per interface cell for vertex interpolation, the isovalue search, the
-# isoface and the swept-face integrals (a fixed per-unit figure, independent of the iteration
-# counts of this implementation)
-FLOP_PER_SURFACE_CELL = 11000.0
+# isoface and the swept-face integrals: those that the kernel of rectangular hexahedra (every workload's
+# here) executes, fused ones counted twice, on the violent box (SQ_INSTS_VALU_ADD_F64, _MUL_F64, _FMA_F64
+# and _TRANS_F64 of 66 dispatches: 0.719, 0.872, 1.672 and 0.130 million of 64 lanes, 58300 cells)
+FLOP_PER_SURFACE_CELL = 5560.0
 COPY_N = 1 << 27  # doubles moved by the calibration copy (1 GiB read, 1 GiB written)
 KERNEL_KEYS = {"k_find_surface": "find_surface", "k_surface": "surface", "k_update": "update",
                "k_bound_sweep": "bound_sweep", "k_bound_group": "bound_group", "k_bound_end": "bound_end",
@@ -227,6 +228,12 @@ def _kernel_key(name):
     return None
 
 
+def _label(key):
+    """The kernel that a profile's key stands for (the interface cells of every profiled workload are
+    rectangular hexahedra)."""
+    return "k_surface_box" if key == "surface" else f"k_{key}"
+
+
 def _pmc_per_dispatch(path, counter):
     import csv
     vals = {}
@@ -272,7 +279,7 @@ def summarize_ensemble_profile():
             continue
         d = by[k]
         tot += sum(d) / steps
-        lines.append(f"k_{k} | {len(d)} | {len(d) / steps:g} | {np.mean(d):.2f} | {min(d):.2f} | {max(d):.2f}")
+        lines.append(f"{_label(k)} | {len(d)} | {len(d) / steps:g} | {np.mean(d):.2f} | {min(d):.2f} | {max(d):.2f}")
     lines.append(f"# kernels per step {tot:.1f} us; the run's events gave {ens['batched_ms_per_step'] * 1e3:.1f} us/step "
                  f"({ens['batched_cell_steps_per_s']:.3e} cell-steps/s, {ens['hbm_frac']:.4f} of the HBM roofline at "
                  f"{ens['bytes_per_cell_step']:.1f} B/cell-step)")
@@ -318,10 +325,10 @@ def summarize_profiles(workload):
             raise SystemExit(f"{k}: {len(d)} dispatches do not split into {passes} steps")
         win = d[(warmup + 1 + steps) * per:(warmup + 1 + 2 * steps) * per]
         means[k] = float(np.mean(win))
-        lines.append(f"k_{k} | {len(win)} | {means[k]:.2f} | {min(win):.2f} | {max(win):.2f}")
+        lines.append(f"{_label(k)} | {len(win)} | {means[k]:.2f} | {min(win):.2f} | {max(win):.2f}")
     if "surface" in means:
         tf = FLOP_PER_SURFACE_CELL * n_s / (means["surface"] * 1e-6) / 1e12
-        lines.append(f"# k_surface: {FLOP_PER_SURFACE_CELL:.0f} flop x {n_s:.0f} interface cells / {means['surface']:.2f} us"
+        lines.append(f"# {_label('surface')}: {FLOP_PER_SURFACE_CELL:.0f} flop x {n_s:.0f} interface cells / {means['surface']:.2f} us"
                      f" = {tf:.3f} TFLOP/s = {tf / FP64_VECTOR_TFLOPS:.4f} of the {FP64_VECTOR_TFLOPS} TFLOP/s FP64 peak"
                      + (f" (the line reported {run['roofline']['frac']:.4f} from its own events)"
                         if run['roofline']['kernel'] == "surface" else ""))
@@ -392,7 +399,7 @@ def summarize_profiles(workload):
             mean = {n: sum(v.values()) / max(len(v), 1) for n, v in per[k].items()}
             nd = len(per[k]["SQ_WAVES"])
             wv = mean["SQ_WAVES"]
-            lines.append(f"k_{k} | {nd} | {wv:.0f} | {mean['SQ_INSTS_VALU'] / wv:.0f} | {mean['SQ_INSTS_SALU'] / wv:.0f} | "
+            lines.append(f"{_label(k)} | {nd} | {wv:.0f} | {mean['SQ_INSTS_VALU'] / wv:.0f} | {mean['SQ_INSTS_SALU'] / wv:.0f} | "
                          f"{mean['SQ_INSTS_VMEM_RD'] / wv:.1f} | {mean['SQ_INSTS_LDS'] / wv:.1f} | "
                          f"{mean['SQ_WAVE_CYCLES'] / wv:.0f} | {mean['SQ_INSTS_VALU']:.4g}")
         open(os.path.join(PROFILES, f"sq_counters_{workload}.txt"), "w").write("\n".join(lines) + "\n")

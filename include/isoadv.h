@@ -27,7 +27,10 @@
  *    pyramids, triangular prisms); and general polyhedra of 4 to 16 faces of 3
  *    to 16 points over at most 32 points (e.g. hexahedra merged across split
  *    faces).  Larger cells give ISO_EUNSUPPORTED.  Every entry point takes
- *    every cell type.
+ *    every cell type.  A mesh whose cells are all rectangular hexahedra with
+ *    edges exactly along the coordinate axes (each coordinate of a cell's
+ *    points one of two values, bit for bit) takes a faster interface kernel;
+ *    one cell that is not sends the whole mesh to the general one.
  *  - Patch kinds: WALL and EMPTY faces carry no flux (their phi is ignored);
  *    INOUT faces carry flux, inflow carrying the patch's alpha_in; CYCLIC
  *    patches come in pairs (face n of a patch matches face n of its partner,

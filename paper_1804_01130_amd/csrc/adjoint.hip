@@ -5,9 +5,10 @@
 // writes them), these launches produce the adjoints of alpha and phi:
 //   prep       per cell: the update's round-off chop, the cells the bounding sweeps start from
 //              (and their first corrections); per face buffers cleared
-//   sweep      one per bounding sweep, grid-wide: the sweeps replayed with a tape (same
-//              arithmetic as the forward)
-//   unsweep    two per sweep, in reverse: the bounding step (end of Section 3.2) transposed
+//   group      the bounding sweeps replayed with a tape (same arithmetic as the forward), then the
+//              bounding step (end of Section 3.2) transposed, sweep by sweep in reverse; on a mesh of
+//              more than 2^17 cells the first sweep is a launch on the whole grid (sweep), and its
+//              reverse two (unsweep)
 //   faces      per cell, a gather over its flux faces: transposes of the flux-form update and of
 //              the bulk fluxes alpha_upwind phi dt; phi's adjoint through dV = phi * (dV/phi); and
 //              the list of interface cells
@@ -166,18 +167,19 @@ struct AdjArgs {
     AdjWork w;
 };
 
-// Bounding replayed with a tape, then reversed, grid-wide: one kernel per forward sweep (phase B of
-// sweep s fused with phase A of sweep s+1, as in the step's own sweeps; phase A of sweep 0 runs in
-// k_adj_prep) and two per reversed sweep.  Tape per sweep s and listed cell (row s*nc + i, i its
-// place in the sweep's list): a, need, sumcap, r, then cap and dV-now per slot; flags (64 bits, for
-// up to 16 slots): bit 0 over, bit 1 r capped at 1, bit 2 sumcap > 0, bit 3+k slot k corrected, bit
-// 19+k slot k read the running dV (corrected in an earlier sweep).  List order never affects a result: each listed cell writes
-// only its own outflow faces and its own tape row, each touched cell only itself.
+// Bounding replayed with a tape, then reversed: one pass per forward sweep (phase B of sweep s fused
+// with phase A of sweep s+1, as in the step's own sweeps; phase A of sweep 0 runs in k_adj_prep) and two
+// per reversed sweep, each a turn of k_adj_group or a launch on the grid.  Tape per sweep s and listed
+// cell (row s*nc + i, i its place in the sweep's list): a, need, sumcap, r, then cap and dV-now per slot;
+// flags (64 bits, for up to 16 slots): bit 0 over, bit 1 r capped at 1, bit 2 sumcap > 0, bit 3+k slot k
+// corrected, bit 19+k slot k read the running dV (corrected in an earlier sweep).  List order never
+// affects a result: each listed cell writes only its own outflow faces and its own tape row, each touched
+// cell only itself.
 //
 // Buffers that start every call at zero and are left so: the face marks (`touched`), two banks of
 // cell marks (sweep s uses bank s&1: phase B of sweep s clears what phase A of sweep s+1 sets in the
-// other bank), and three rotating correction buffers (sweep s writes s%3, the kernel of sweep s+1
-// reads it and clears s-1's).
+// other bank), and three rotating correction buffers (sweep s writes s%3, sweep s+1 reads it and clears
+// s-1's).
 
 // Phase A of sweep s for listed cell P, row `row` of the sweep's list, with bounding state a: the
 // correction of each outflow face and the tape row; the cells it touches come back through tsel.
@@ -350,7 +352,7 @@ __device__ __forceinline__ void adj_sweep(const AdjArgs &A, int s, int b0, int s
     const DevMesh &m = A.m;
     const AdjWork &w = A.w;
     const bool last = s == A.n_iter - 1;
-    if (s >= 1) {  // sweep s-1's corrections were read by the previous kernel: clear them
+    if (s >= 1) {  // sweep s-1's corrections were read before this sweep: clear them
         const int np = adj_count(A, kAdjL + s - 1);
         double *stale = w.delta + (size_t)((s - 1) % 3) * nf;
         for (int i = b0 + threadIdx.x; i < np; i += stride) {
@@ -541,7 +543,7 @@ __device__ __forceinline__ void adj_unsweep_correct(const AdjArgs &A, int s, int
 // out of bounds, a sixth of those touched).  From k_adj_prep to k_adj_faces in us, nine launches / one group
 // whatever the length / this: random fields on 64x32x32 (737 cells out of bounds) 65 / 78 / 65, on 64x64x32
 // (979) 67 / 106 / 86, on 192x96x96 the violent start (1148) 109 / 159 / 132, after 20 steps on 64x64x32 (132)
-// 102 / 26 / 27.
+// 54 (its kernels alone) / 26 / 27.
 // A traced step and adjoint of 128x64x64 cells and the gradient of five 256x128 slab steps: nine launches
 // 252 and 845 us, one group (and the gathers of k_adj_faces straight-line) 221 and 750, with the loads of
 // a sweep's cell batched, none behind a branch, 205 and 660 (this kernel on the slab 18.3 -> 11.9; on the box
@@ -1289,6 +1291,7 @@ __device__ __forceinline__ double adj_alpha_big(const double *gb) {
 // their stencils.  A cell that shares a class twice (two of its vertices are periodic images of
 // one point) appears twice in the class's stencil, with one weight per image; its vertices are
 // summed at its first entry and each of its distinct classes is taken once.
+
 // The sum of class k over its stencil, of fixed width kN (a mesh of rectangular hexahedra): whole stencils by
 // 16-byte loads (a class's entries one by one ask for the same lines eight times over: 24.4 us, this 10.5, on
 // 128x64x64 cells).  Their padding repeats the first entry.

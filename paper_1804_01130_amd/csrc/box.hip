@@ -13,8 +13,11 @@
 // What bounds it: on small meshes the chain of one wave (about 3000 VALU instructions, half of them FP64
 // arithmetic at four cycles each or eight when dependent, and five dependent loads of 1 us each); on
 // large ones also the vector caches (the stencils' 96 bytes of each vertex).  Against the general
-// kernel's eight lanes per cell (about 4900 VALU instructions per wave of 8 cells): 16.5 us instead of
-// 26.5 for 74 interface cells, 28 us instead of 100 for the 44.6k of the 256x128x128 box.
+// kernel's eight lanes per cell (about 4900 VALU instructions per wave of 8 cells): 13.5 us instead of
+// 26.0 for 72 interface cells of a slab, 16 instead of 27.9 for 1136, 25.3 instead of 97.9 for the 46.5k of
+// the 256x128x128 box.  Rounding: of one step of 90 graded boxes against 80-bit arithmetic, the largest error
+// of a box is on average 0.77 of the general kernel's and its root mean square 0.81 (the reciprocals and
+// roots below are good to a unit in the last place, but there are fewer operations).
 // Two lanes rather than one or eight: one lane would halve the waves, which at 45k cells are already
 // only 1.4 per SIMD, and eight would spend most of each wave on the same scalar steps of the search.
 #include "device_common.h"
@@ -348,8 +351,9 @@ __device__ __forceinline__ void gather_velocity(const SurfArgs &A, const int (&a
     for (int i = 0; i < 3; ++i) us[i] = fma(w[1], uv[1][i], w[0] * uv[0][i]);
 }
 
-// Work-groups of one wave: the list's waves then spread evenly over the CUs (1116 interface cells of a slab
-// 17.0 us against 19.7 with 256 threads, 45k of a box 28.2 against 30.0).
+// Work-groups of one wave: the list's waves then spread evenly over the CUs (1136 interface cells of a slab
+// 16.1 us against 18.6 with 256 threads, 46.5k of a box 25.3 against 26.1, interpolated velocities on 4147 cells
+// of a box 16.1 against 20.4).
 constexpr int kBlock = 64, kGroups = kBlock / 2;  // threads and interface cells of a work-group
 
 // kInterp: U_S by cell-point interpolation (us_mode 1) instead of U_P.

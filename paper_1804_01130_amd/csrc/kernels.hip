@@ -12,14 +12,17 @@
 //                  outflow face (Eqs. tv .. intaplus) -> dV (each face has one upwind cell: no
 //                  atomics).  Meshes of rectangular hexahedra have a kernel of their own (box.hip,
 //                  two lanes per cell).  Interface cells that are general polyhedra go to
-//                  theirs (big.hip), launched on a side stream beside this one
+//                  theirs (big.hip), launched on a side stream beside this one, as is the box
+//                  kernel in ensembles that have other cells too
 //   update         per cell, gather over its flux faces in ascending face id: dV from the
 //                  interface kernel or alpha_upwind*phi*dt; alpha - sum/V; round-off chopping;
 //                  cells outside the bounds are listed and compute the first sweep's corrections
-//   bound          one kernel per Jacobi sweep: the touched cells apply the sweep's corrections in
-//                  face order with chopping, and those still outside the bounds compute the next
-//                  sweep's (bounding step at the end of Section 3.2); a one-group kernel leaves
-//                  the workspace clean
+//   bound          Jacobi sweeps: the touched cells apply the sweep's corrections in face order
+//                  with chopping, and those still outside the bounds compute the next sweep's
+//                  (bounding step at the end of Section 3.2).  k_bound_group runs them all and
+//                  leaves the workspace clean; on a mesh of more than 2^17 cells the first, and
+//                  in an ensemble of as many every one, is a launch on the whole grid
+//                  (k_bound_sweep), there with a one-group kernel at the end
 // Nothing in the step is a dense contraction, so no matrix instructions are used.
 #include <hip/hip_runtime.h>
 
@@ -1130,7 +1133,7 @@ struct BoundArgs {
 // (B) every touched cell applies the corrections of its faces in ascending face order.  Phase A
 // of a cell needs only its own new alpha and its own outflow faces, so a cell still out of bounds
 // after phase B of sweep s runs phase A of sweep s+1 at once: one pass per sweep (phase A of sweep
-// 0 runs inside the update), a launch or a turn of k_bound_group.  Touched lists and marks
+// 0 runs inside the update), a launch of k_bound_sweep or a turn of k_bound_group.  Touched lists and marks
 // alternate between two banks, counter slots rotate over four.  List order never affects a result.
 
 // Where a sweep finds and leaves its counts: the counter slots in memory, or a work-group's own.
