@@ -178,7 +178,10 @@ __device__ __forceinline__ int wave_append(int count, int32_t *counter) {
     return base + incl - count;
 }
 
-// The same for three counters (up to 2^20 elements of a wave each), their atomics in flight together.
+// The same for three counters (up to 2^20 elements of a wave each), their atomics in flight together.  A count
+// of zero takes none: cells out of bounds often have nothing to correct, and where thousands of waves append,
+// their atomics on one line are what bounds them (the update of 128x64x64 cells, a tenth of them out of bounds:
+// 232 us with an atomic of each wave for each counter, 138 without those of zero; a thousandth: 26 and 21).
 __device__ __forceinline__ int3 wave_append3(int3 count, int32_t *cx, int32_t *cy, int32_t *cz) {
     const int lane = __lane_id();
     const int top = 63 - __clzll((unsigned long long)__ballot(1));
@@ -190,10 +193,11 @@ __device__ __forceinline__ int3 wave_append3(int3 count, int32_t *cx, int32_t *c
         if (lane >= o) incl += y;
     }
     int3 b = make_int3(0, 0, 0);
-    if (lane == top && incl) {
-        b.x = atomicAdd(cx, (int)(incl & 0xFFFFF));
-        b.y = atomicAdd(cy, (int)((incl >> 20) & 0xFFFFF));
-        b.z = atomicAdd(cz, (int)(incl >> 40));
+    if (lane == top) {
+        const int nx = (int)(incl & 0xFFFFF), ny = (int)((incl >> 20) & 0xFFFFF), nz = (int)(incl >> 40);
+        if (nx) b.x = atomicAdd(cx, nx);
+        if (ny) b.y = atomicAdd(cy, ny);
+        if (nz) b.z = atomicAdd(cz, nz);
     }
     const uint64_t before = incl - own;
     return make_int3(__shfl(b.x, top, 64) + (int)(before & 0xFFFFF), __shfl(b.y, top, 64) + (int)((before >> 20) & 0xFFFFF),
