@@ -1458,7 +1458,7 @@ hipError_t launch_adj_w(const AdjArgs &a, hipStream_t s) {
     for (int it = 0; it < grid; ++it) hipLaunchKernelGGL(k_adj_sweep<W>, dim3(gb), dim3(256), 0, s, a, it);
     const int gt = adj_group_threads(W);
     if (grid < a.n_iter)
-        hipLaunchKernelGGL(k_adj_group<W>, dim3(std::min(kBoundGroups, (n + gt - 1) / gt)), dim3(gt), 0, s, a, grid);
+        hipLaunchKernelGGL(k_adj_group<W>, dim3(std::min(kAdjBoundGroups, (n + gt - 1) / gt)), dim3(gt), 0, s, a, grid);
     for (int it = grid - 1; it >= 0; --it) {
         hipLaunchKernelGGL(k_adj_unsweep_apply<W>, dim3(gb), dim3(256), 0, s, a, it);
         hipLaunchKernelGGL(k_adj_unsweep_correct<W>, dim3(gb), dim3(256), 0, s, a, it);

@@ -150,9 +150,10 @@ enum : int {
     kCntActive0 = 6,    // n_bound_active of the last step
     kCntFaces = 7,      // flist length
     kCntBound = 16,     // [16, 24): four rotating slots of per-sweep bounding counters
-    kCntGroups = 24,    // work-groups of a bounding launch that are done, zero between launches
-    kCntNum = 32
+    kCntTeam = 32,      // [32, 48): the work-groups that share long bounding sweeps (Team), zero between steps
+    kCntNum = 48
 };
+constexpr int kTeamWords = 16;
 
 struct StepArgs {
     const double *alpha;
@@ -184,10 +185,14 @@ struct Params {
 };
 
 // Bounding sweeps (k_bound_group has the reasons): cells of a mesh above which the first sweep is a launch of
-// its own, touched cells that one work-group walks alone, the work-groups for more, and their threads for W flux
-// slots.
-constexpr int kBoundGroupCells = 1 << 17;
-constexpr int kBoundAlone = 512, kBoundGroups = 32;
+// its own, touched cells of the first sweep that one work-group walks alone, and, for W flux slots, the
+// work-groups of a launch and their threads.
+constexpr int kBoundGroupCells = 1 << 17, kBoundAlone = 512;
+constexpr int kAdjBoundGroups = 32;
+constexpr int bound_groups(int n, int W, int threads) {
+    const int most = n > 1 << 18 ? 128 : W > 8 ? 64 : 32, all = (n + threads - 1) / threads;
+    return all < most ? all : most;
+}
 constexpr int bound_threads(int W) { return W > 8 ? 512 : 1024; }
 
 // Adjoint workspace (device pointers; allocated by a plan on its first adjoint step).  S = number of

@@ -1299,8 +1299,9 @@ __global__ void __launch_bounds__(256) k_bound_sweep(BoundArgs A, int it) {
 
 // End of the step, by one work-group: chop the listed cells when no sweep ran, clear the correction
 // buffer of the last sweep (`nd` corrections; the last sweep itself has cleared the face marks), keep
-// this step's counters for the statistics and zero them for the next step.
-__device__ __forceinline__ void bound_end(const BoundArgs &A, int nd) {
+// this step's counters for the statistics and zero them for the next step (`keep` not yet: the length by which
+// groups that arrive late still tell a long list).
+__device__ __forceinline__ void bound_end(const BoundArgs &A, int nd, const int32_t *keep) {
     const int tid = threadIdx.x, nt = blockDim.x;
     const int nf = A.m.n_faces;
     int32_t *counters = A.w.counters;
@@ -1325,51 +1326,85 @@ __device__ __forceinline__ void bound_end(const BoundArgs &A, int nd) {
     if (tid < 8) counters[8 + tid] = tid == kCntActive0 ? counters[kCntOff] : counters[tid];
     __syncthreads();
     if (tid < 8) counters[tid] = 0;
-    if (tid >= kCntBound && tid < kCntBound + 8) counters[tid] = 0;
+    if (tid >= kCntBound && tid < kCntBound + 8 && counters + tid != keep) counters[tid] = 0;
 }
 
 __global__ void __launch_bounds__(1024) k_bound_end(BoundArgs A) {
-    bound_end(A, A.n_iter > 0 ? bound_slot(A.w.counters, A.n_iter - 1)[kSlotDelta] : 0);
+    bound_end(A, A.n_iter > 0 ? bound_slot(A.w.counters, A.n_iter - 1)[kSlotDelta] : 0, nullptr);
 }
 
 // The sweeps from `first` on and the end of the step in one launch.  What a sweep costs is its launch and one
 // chain of dependent loads, as long as its list is short: up to kBoundAlone touched cells one work-group walks
-// it alone, its counts in LDS, and the others leave at once.  A longer list wants more of the chip: all
-// kBoundGroups groups walk sweep `first`, in strides that give each a part, and the last to end (nobody waits)
-// goes on alone, as the sweeps after it have a tenth of its cells or fewer.  What it has to see of the
-// others' stores costs some 5 us, a launch 1.5; so above kBoundGroupCells, where the first list is nearly always
-// long, the first sweep is a launch of its own on the whole grid, and `first` is the second.  The sweeps of an
-// ensemble all are, as their lists are those of its members together.
+// it alone, its counts in LDS, and the others leave at once.  A longer list wants more of the chip: the groups of
+// the launch share the sweeps (Team) until one has a stride of the leader's threads or less, which then goes on
+// alone.  What they have to see of each other's stores costs some 12 us a sweep, a launch 1.5; so above
+// kBoundGroupCells, where the first list is nearly always long, the first sweep is a launch of its own on the
+// whole grid, and `first` is the second.  The sweeps of an ensemble all are, as their lists are those of its
+// members together.  Launches for every sweep that leave at once when one group has done the work cost 1.3 to
+// 1.8 us each, 3 to 4 us of a calm step of 26 to 37.
 // Bounding stage in us (events), all sweeps on the grid / by one group whatever the length / this:
-//   calm slab 384x96 11.5 / 6.3 / 6.4, box 64x32x32 11.5 / 6.5 / 6.5, slab 1024x256 12.4 / 10.9 / 11.0
-//   random fields (cells out of bounds) on 64x32x32: (107) 13.2 / 10.0 / 10.5, (338) 21.0 / 20.9 / 17.0,
-//   (737) 21.2 / 33 / 18.7; on 64x64x32: (257) 20.4 / 18.8 / 16.2, (979) 21.8 / 43.6 / 20.0;
-//   on 128x64x64 (5582) 24.8 / 35.0 / 34;
+//   calm slab 384x96 11.5 / 8.2 / 8.9, box 64x32x32 11.2 / 6.8 / 6.5, slab 1024x256 12.2 / 10.8 / 11.1
+//   random fields (cells out of bounds) on 64x32x32: (107) 13.0 / 10.1 / 10.4, (338) 20.0 / 21.2 / 19.9,
+//   (509) 20.8 / 26.6 / 21.2; on 64x64x32: (257) 20.4 / 19.5 / 19.1, (441) 21.5 / 26.7 / 20.8;
 //   100 steps of the violent 256x128x128 box (440 to 2848) 31.6 on average and 41 at most / 27.8 and 134 /
-//   27 and 64.
-// By kBoundAlone 256, 512 or 1024 for 64x32x32 (338): 17.3, 17.0, 21.4; by 16, 32 or 128 groups for calm
-// lists, which then leave at once: +0.1, +0.2, +1 us.
+//   26.7 and 51.
+// The step, from fields out of bounds in every sweep: 64x32x32 (855) 79 / 75 / 72, (7.9 k) 98 / 390 / 95,
+//   64x64x32 (1.8 k) 98 / 157 / 84, (62 k, half of all) 103 / 1366 / 138, 256x128x128 (63 k) 638 / 3897 / 588,
+//   (1.9 M) 1730 / 40050 / 1778, polyhedra 64x32x32 (3.8 k) 133 / 473 / 139, (15 k) 65 / 906 / 76.
+// The work-groups, 32 / 64 / 128: 128x64x64 (68 k) 326 / 325 / 305, 256x128x128 (1.9 M) 2464 / 1901 / 1778, calm,
+// where they leave at once, +0.2 / +0.4 / +1; polyhedra 128x64x64 (202 k cells, 111 k) 272 / 218 / 200, but not more
+// than 64 for their half-sized groups below 2^18 cells, where 128 cost as much in calm steps.  Four groups or fewer
+// (4096 cells) do not share: one walks a list in as many strides.
 template <int W, bool kAvg>
 __global__ void __launch_bounds__(bound_threads(W)) k_bound_group(BoundArgs A, int first) {
     __shared__ int32_t cnt[2][4], faces;
-    int32_t *counters = A.w.counters;
-    const int tid = threadIdx.x, bd = blockDim.x;
+    int32_t *counters = A.w.counters, *len = &bound_slot(counters, first)[kSlotTouched];
+    const int tid = threadIdx.x, bd = blockDim.x, n0 = *len;
     int it = first, stale = first > 0 ? bound_slot(counters, first - 1)[kSlotDelta] : 0;
-    const int nT = bound_slot(counters, first)[kSlotTouched];
-    if (__builtin_expect(nT > kBoundAlone && gridDim.x > 1, 0)) {
-        int32_t *next = bound_slot(counters, first + 1);
-        const int nd = bound_slot(counters, first)[kSlotDelta], width = min((nT / (int)gridDim.x + 64) & ~63, bd);
-        if (tid < width)
-            bound_sweep<W, kAvg>(A, first, blockIdx.x * width, gridDim.x * width,
-                                 {stale, nT, counters[kCntFaces], &next[kSlotDelta], &next[kSlotTouched], &counters[kCntFaces]});
-        if (!last_group(&counters[kCntGroups])) return;
-        ++it;
-        stale = nd;
+    const int32_t *from = bound_slot(counters, first);  // sweep `it`'s list lengths
+    // (a long list's length stays until every group of the launch has left; a short one's is read as it is or zero)
+    const bool team = __builtin_expect(n0 > kBoundAlone && gridDim.x > 4, 0);
+    Team *t = reinterpret_cast<Team *>(counters + kCntTeam);
+    if (team) {
+        bool lead = false;
+        const int tiles0 = team_tiles(n0);
+        for (uint32_t sum = tiles0;;) {
+            const bool over = team_work(t, tiles0, lead, [&](int i) {
+                const bool f = team_load(&t->word) == 0;
+                const int s = f ? first : team_load(&t->arg[0]), nd = f ? stale : team_load(&t->arg[1]),
+                          nT = f ? n0 : team_load(&t->arg[2]), tiles = team_tiles(nT), width = team_width(nT, tiles);
+                int32_t *next = t->cnt[(s + 1) & 1];
+                if (tid < width)
+                    bound_sweep<W, kAvg>(A, s, i * width, tiles * width, {nd, nT, team_load(&counters[kCntFaces]),
+                                         &next[kSlotDelta], &next[kSlotTouched], &counters[kCntFaces]});
+            });
+            if (over) {
+                if (team_leave(t)) *len = 0;
+                return;
+            }
+            if (!lead) {
+                __builtin_amdgcn_s_sleep(4);
+                continue;
+            }
+            team_close(t, sum);
+            stale = team_load(&from[kSlotDelta]);
+            from = t->cnt[++it & 1];
+            const int nT = team_load(&from[kSlotTouched]);
+            if (it == A.n_iter || nT <= bd) break;
+            if (tid == 0) {
+                const int32_t arg[3] = {it, stale, nT};
+                for (int i = 0; i < 3; ++i) t->arg[i] = arg[i];
+                for (int i = 0; i < 2; ++i) t->cnt[(it + 1) & 1][i] = 0;
+            }
+            team_open(t, team_tiles(nT));
+            sum += team_tiles(nT);
+        }
+        team_dismiss(t);
     } else if (blockIdx.x != 0) {
         return;
     }
-    if (tid < 2) cnt[it & 1][tid] = load_shared(&bound_slot(counters, it)[tid]);
-    if (tid == 2) faces = load_shared(&counters[kCntFaces]);
+    if (tid < 2) cnt[it & 1][tid] = team_load(&from[tid]);
+    if (tid == 2) faces = team_load(&counters[kCntFaces]);
     for (; it < A.n_iter; ++it) {
         int32_t *now = cnt[it & 1], *next = cnt[(it + 1) & 1];
         if (tid < 2) next[tid] = 0;
@@ -1381,7 +1416,8 @@ __global__ void __launch_bounds__(bound_threads(W)) k_bound_group(BoundArgs A, i
         __syncthreads();
     }
     if (tid == 2) counters[kCntFaces] = faces;
-    bound_end(A, stale);
+    bound_end(A, stale, team ? len : nullptr);
+    if (team && team_leave(t)) *len = 0;
 }
 
 // Step statistics in two passes with a fixed order of summation (results do not depend on timing):
@@ -1458,7 +1494,7 @@ void launch_wide(const DevMesh &m, const UpdArgs &ua, const BoundArgs &ba, const
     for (int it = 0; it < grid; ++it)
         hipLaunchKernelGGL((k_bound_sweep<W, kAvg>), dim3(cfg.bound_blocks), dim3(256), 0, s, ba, it);
     if (grid < ba.n_iter) {
-        const int bt = bound_threads(W), gb = std::min(kBoundGroups, (m.n_cells + bt - 1) / bt);
+        const int bt = bound_threads(W), gb = bound_groups(m.n_cells, W, bt);
         hipLaunchKernelGGL((k_bound_group<W, kAvg>), dim3(gb), dim3(bt), 0, s, ba, grid);
         return;
     }
