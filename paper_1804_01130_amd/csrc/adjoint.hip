@@ -539,11 +539,12 @@ __device__ __forceinline__ void adj_unsweep_correct(const AdjArgs &A, int s, int
 
 // The sweeps on the grid, and all from `first` on, forwards and back, in one launch, as in k_bound_group of the
 // step (whose lists these are): a short list costs its launch and a chain of loads, so one work-group walks it
-// alone; a long first list, forwards, all do (the way back stays with the last of them: its lists are the cells
-// out of bounds, a sixth of those touched).  From k_adj_prep to k_adj_faces in us, nine launches / one group
-// whatever the length / this: random fields on 64x32x32 (737 cells out of bounds) 65 / 78 / 65, on 64x64x32
-// (979) 67 / 106 / 86, on 192x96x96 the violent start (1148) 109 / 159 / 132, after 20 steps on 64x64x32 (132)
-// 54 (its kernels alone) / 26 / 27.
+// alone; a long first list is shared, and so are the sweeps after it and those on the way back while their lists
+// have more cells than a group has threads (Team).  An adjoint in us, one group whatever the length / this: calm
+// 64x32x32 and 128x64x64 39.9 / 40.2 and 125.8 / 126.2, the violent start on 192x96x96 (1148 cells out of bounds)
+// 406 / 364.  Step and adjoint, nine launches / one group / this, from fields out of bounds in every sweep:
+// 64x32x32 (855) 266 / 289 / 215, (7.9 k) 296 / 1737 / 265, 128x64x64 (68 k) 780 / 10900 / 773, 256x128x128 (1.9 M)
+// 4431 / 215000 / 5389, polyhedra 64x32x32 (3.8 k) 515 / 2060 / 475.
 // A traced step and adjoint of 128x64x64 cells and the gradient of five 256x128 slab steps: nine launches
 // 252 and 845 us, one group (and the gathers of k_adj_faces straight-line) 221 and 750, with the loads of
 // a sweep's cell batched, none behind a branch, 205 and 660 (this kernel on the slab 18.3 -> 11.9; on the box
@@ -563,26 +564,66 @@ __global__ void __launch_bounds__(256) k_adj_unsweep_correct(AdjArgs A, int s) {
 constexpr int adj_group_threads(int W) { return W > 8 ? 256 : W > 4 ? 512 : 1024; }  // (its registers fit)
 template <int W>
 __global__ void __launch_bounds__(adj_group_threads(W)) k_adj_group(AdjArgs A, int first) {
-    const int t = threadIdx.x, nt = blockDim.x, nT = adj_count(A, kAdjT + first);
-    int s0 = first;
-    if (__builtin_expect(nT > kBoundAlone && gridDim.x > 1, 0)) {
-        const int width = min((nT / (int)gridDim.x + 64) & ~63, nt);
-        if (t < width) adj_sweep<W>(A, first, blockIdx.x * width, gridDim.x * width);
-        if (!last_group(&A.w.counters[kAdjGroups])) return;
-        ++s0;
-    } else if (blockIdx.x != 0) {
+    const int tid = threadIdx.x, bd = blockDim.x, n0 = adj_count(A, kAdjT + first);
+    if (__builtin_expect(n0 <= kBoundAlone || gridDim.x <= 4, 1)) {
+        if (blockIdx.x != 0) return;
+        for (int s = first; s < A.n_iter; ++s) {
+            adj_sweep<W>(A, s, 0, bd);
+            __syncthreads();
+        }
+        for (int s = A.n_iter - 1; s >= first; --s) {
+            adj_unsweep_apply<W>(A, s, tid, bd);
+            __syncthreads();
+            adj_unsweep_correct<W>(A, s, tid, bd);
+            __syncthreads();
+        }
         return;
     }
-    for (int s = s0; s < A.n_iter; ++s) {
-        adj_sweep<W>(A, s, 0, nt);
-        __syncthreads();
+    // the phases: m sweeps, and two for each of them on the way back; the items of one, and its part i of `tiles`
+    const int m = A.n_iter - first;
+    const auto sweep = [&](int p) { return p < m ? first + p : A.n_iter - 1 - (p - m) / 2; };
+    const auto items = [&](int p) { return adj_count(A, (p < m ? kAdjT : kAdjL) + sweep(p)); };
+    const auto part = [&](int p, int i, int tiles, int width) {
+        const int s = sweep(p), b0 = i * width, stride = tiles * width;
+        if (tid >= width) return;
+        if (p < m) adj_sweep<W>(A, s, b0, stride);
+        else if (((p - m) & 1) == 0) adj_unsweep_apply<W>(A, s, b0 + tid, stride);
+        else adj_unsweep_correct<W>(A, s, b0 + tid, stride);
+    };
+    Team *t = reinterpret_cast<Team *>(A.w.counters + kAdjTeam);
+    const int tiles0 = team_tiles(n0);
+    bool lead = false;
+    int p = 0;
+    for (uint32_t sum = tiles0;;) {
+        const bool over = team_work(t, tiles0, lead, [&](int i) {
+            const bool f = team_load(&t->word) == 0;  // the first phase
+            const int n = f ? n0 : team_load(&t->arg[1]), tiles = team_tiles(n);
+            part(f ? 0 : team_load(&t->arg[0]), i, tiles, team_width(n, tiles));
+        });
+        if (over) {
+            team_leave(t);
+            return;
+        }
+        if (!lead) {
+            __builtin_amdgcn_s_sleep(4);
+            continue;
+        }
+        team_close(t, sum);
+        int n = 0;
+        for (++p; p < 3 * m && (n = items(p)) <= bd; ++p) {
+            part(p, 0, 1, bd);
+            __syncthreads();
+        }
+        if (p == 3 * m) break;
+        if (tid == 0) {
+            t->arg[0] = p;
+            t->arg[1] = n;
+        }
+        team_open(t, team_tiles(n));
+        sum += team_tiles(n);
     }
-    for (int s = A.n_iter - 1; s >= first; --s) {
-        adj_unsweep_apply<W>(A, s, t, nt);
-        __syncthreads();
-        adj_unsweep_correct<W>(A, s, t, nt);
-        __syncthreads();
-    }
+    team_dismiss(t);
+    team_leave(t);
 }
 
 // per cell: transposes of the update (through the round-off chop) and of the bulk fluxes
@@ -1458,7 +1499,7 @@ hipError_t launch_adj_w(const AdjArgs &a, hipStream_t s) {
     for (int it = 0; it < grid; ++it) hipLaunchKernelGGL(k_adj_sweep<W>, dim3(gb), dim3(256), 0, s, a, it);
     const int gt = adj_group_threads(W);
     if (grid < a.n_iter)
-        hipLaunchKernelGGL(k_adj_group<W>, dim3(std::min(kAdjBoundGroups, (n + gt - 1) / gt)), dim3(gt), 0, s, a, grid);
+        hipLaunchKernelGGL(k_adj_group<W>, dim3(bound_groups(n, W, gt)), dim3(gt), 0, s, a, grid);
     for (int it = grid - 1; it >= 0; --it) {
         hipLaunchKernelGGL(k_adj_unsweep_apply<W>, dim3(gb), dim3(256), 0, s, a, it);
         hipLaunchKernelGGL(k_adj_unsweep_correct<W>, dim3(gb), dim3(256), 0, s, a, it);

@@ -204,22 +204,6 @@ __device__ __forceinline__ int3 wave_append3(int3 count, int32_t *cx, int32_t *c
                      __shfl(b.z, top, 64) + (int)(before >> 40));
 }
 
-// Whether this work-group is the last of its launch to come here, all of it; `count`, zero before, is left
-// zero.  The last one then sees what every group stored before it came.  (No group waits for another.)
-__device__ __forceinline__ bool last_group(int32_t *count) {
-    __shared__ bool last;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        __threadfence();
-        last = atomicAdd(count, 1) == (int)gridDim.x - 1;
-        if (last) {
-            *count = 0;
-            __threadfence();
-        }
-    }
-    __syncthreads();
-    return last;
-}
 // ------------------------------------------------------------------------------------------ teams
 // A launch whose work-groups share a chain of phases, cut into tiles.  The tiles of the first phase are drawn by
 // ticket; whoever holds the first ticket leads: it works through every tile that nobody else takes, waits only

@@ -188,7 +188,6 @@ struct Params {
 // its own, touched cells of the first sweep that one work-group walks alone, and, for W flux slots, the
 // work-groups of a launch and their threads.
 constexpr int kBoundGroupCells = 1 << 17, kBoundAlone = 512;
-constexpr int kAdjBoundGroups = 32;
 constexpr int bound_groups(int n, int W, int threads) {
     const int most = n > 1 << 18 ? 128 : W > 8 ? 64 : 32, all = (n + threads - 1) / threads;
     return all < most ? all : most;
@@ -198,9 +197,9 @@ constexpr int bound_threads(int W) { return W > 8 ? 512 : 1024; }
 // Adjoint workspace (device pointers; allocated by a plan on its first adjoint step).  S = number of
 // bounding sweeps (at least 1), nc cells, nf faces.
 // adjoint counters: the interface cells, the polyhedra's (cell, direction) pairs to differentiate
-// along, the work-groups of a bounding launch that are done (zero between launches), then per sweep s the length of its list of
-// cells out of bounds (kAdjL + s) and of the cells its corrections touch (kAdjT + s)
-enum : int { kAdjCells = 2, kAdjDirsBig = 3, kAdjGroups = 4, kAdjGBig = 68, kAdjL = 8, kAdjT = 40, kAdjNum = 72, kAdjMaxSweeps = 31, kAdjG = 9,
+// along, per sweep s the length of its list of cells out of bounds (kAdjL + s) and of the cells its corrections
+// touch (kAdjT + s), then the work-groups that share long sweeps (Team, zero between launches)
+enum : int { kAdjCells = 2, kAdjDirsBig = 3, kAdjGBig = 68, kAdjL = 8, kAdjT = 40, kAdjTeam = 72, kAdjNum = 88, kAdjMaxSweeps = 31, kAdjG = 9,
              kAdjBoundBlocks = 512 };
 struct AdjWork {
     int32_t *counters = nullptr;  // [kAdjNum]

@@ -2,8 +2,9 @@
 plans do that share such lists between work-groups at the same time.
 
 The times are held against a step of the same mesh as an ensemble of one member, whose sweeps are launches on the
-whole grid, best of five each.  The bound is 3 times: a work-group that walks such lists alone takes more than 10,
-sharing them some 1.1."""
+whole grid, best of five each.  Bounds of 3 for the step and 12 for the adjoint (a traced step, sweeps forwards and
+back): a work-group that walks such lists alone takes more than 10 and 50 times the ensemble's step, sharing them
+some 1.1 and 3 times."""
 import numpy as np
 import pytest
 
@@ -54,22 +55,25 @@ def test_cost_of_long_lists():
 
     member()
     assert torch.equal(out, x)
+    bar = to_dev(np.random.default_rng(4).standard_normal(n))
     grid = _best(member)
     step = _best(lambda: plan.step(a, dphi, dU, w.dt, out=out))
-    say(f"[gpu] {n} cells, half of them out of bounds: ensemble {grid * 1e3:.0f} us, step {step * 1e3:.0f}")
-    assert step < 3.0 * grid
+    adjoint = _best(lambda: plan.adjoint(a, dphi, dU, w.dt, bar))
+    say(f"[gpu] {n} cells, half of them out of bounds: ensemble {grid * 1e3:.0f} us, step {step * 1e3:.0f}, "
+        f"adjoint {adjoint * 1e3:.0f}")
+    assert step < 3.0 * grid and adjoint < 12.0 * grid
 
 
 def test_plans_on_several_streams():
-    """Steps of four plans at once, each on a stream of its own, against the same one by one."""
+    """Steps and adjoints of four plans at once, each on a stream of its own, against the same one by one."""
     import torch
     w = W.violent_3d(nx=64, ny=32, nz=32, steps=1)
     n = w.mesh.n_cells
     phi, U = w.phi_U(0)
-    dphi, dU = to_dev(phi), to_dev(U)
+    dphi, dU, bar = to_dev(phi), to_dev(U), to_dev(np.random.default_rng(4).standard_normal(n))
     fields = [to_dev(np.roll(_field(n), 97 * i)) for i in range(4)]
     plans = [gpu_plan(w.mesh, n_bound_iter=5) for _ in range(4)]
-    go = lambda p, a: p.step(a, dphi, dU, 4.0 * w.dt)[0]
+    go = lambda p, a: (p.step(a, dphi, dU, 4.0 * w.dt)[0], *p.adjoint(a, dphi, dU, 4.0 * w.dt, bar))
     ref = [go(plans[0][1], a) for a in fields]
     torch.cuda.synchronize()
     streams = [torch.cuda.Stream() for _ in range(4)]
@@ -81,4 +85,4 @@ def test_plans_on_several_streams():
                 got.append(go(p, a))
         torch.cuda.synchronize()
         for r, g in zip(ref, got):
-            assert torch.equal(r, g)
+            assert all(torch.equal(x, y) for x, y in zip(r, g))
