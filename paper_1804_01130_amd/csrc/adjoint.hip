@@ -543,8 +543,8 @@ __device__ __forceinline__ void adj_unsweep_correct(const AdjArgs &A, int s, int
 // have more cells than a group has threads (Team).  An adjoint in us, one group whatever the length / this: calm
 // 64x32x32 and 128x64x64 39.9 / 40.2 and 125.8 / 126.2, the violent start on 192x96x96 (1148 cells out of bounds)
 // 406 / 364.  Step and adjoint, nine launches / one group / this, from fields out of bounds in every sweep:
-// 64x32x32 (855) 266 / 289 / 215, (7.9 k) 296 / 1737 / 265, 128x64x64 (68 k) 780 / 10900 / 773, 256x128x128 (1.9 M)
-// 4431 / 215000 / 5389, polyhedra 64x32x32 (3.8 k) 515 / 2060 / 475.
+// 64x32x32 (855) 266 / 289 / 207, (7.9 k) 296 / 1737 / 256, 128x64x64 (68 k) 780 / 10900 / 752, 256x128x128 (1.9 M)
+// 4431 / 215000 / 5398, polyhedra 64x32x32 (3.8 k) 515 / 2060 / 464.
 // A traced step and adjoint of 128x64x64 cells and the gradient of five 256x128 slab steps: nine launches
 // 252 and 845 us, one group (and the gathers of k_adj_faces straight-line) 221 and 750, with the loads of
 // a sweep's cell batched, none behind a branch, 205 and 660 (this kernel on the slab 18.3 -> 11.9; on the box

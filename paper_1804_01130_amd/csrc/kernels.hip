@@ -1343,14 +1343,14 @@ __global__ void __launch_bounds__(1024) k_bound_end(BoundArgs A) {
 // members together.  Launches for every sweep that leave at once when one group has done the work cost 1.3 to
 // 1.8 us each, 3 to 4 us of a calm step of 26 to 37.
 // Bounding stage in us (events), all sweeps on the grid / by one group whatever the length / this:
-//   calm slab 384x96 11.5 / 8.2 / 8.9, box 64x32x32 11.2 / 6.8 / 6.5, slab 1024x256 12.2 / 10.8 / 11.1
-//   random fields (cells out of bounds) on 64x32x32: (107) 13.0 / 10.1 / 10.4, (338) 20.0 / 21.2 / 19.9,
-//   (509) 20.8 / 26.6 / 21.2; on 64x64x32: (257) 20.4 / 19.5 / 19.1, (441) 21.5 / 26.7 / 20.8;
+//   calm slab 384x96 11.5 / 8.2 / 9.7, box 64x32x32 11.2 / 6.8 / 6.9, slab 1024x256 12.2 / 10.8 / 11.5
+//   random fields (cells out of bounds) on 64x32x32: (107) 13.0 / 10.1 / 10.9, (338) 20.0 / 21.2 / 20.3,
+//   (509) 20.8 / 26.6 / 20.9; on 64x64x32: (257) 20.4 / 19.5 / 18.6, (441) 21.5 / 26.7 / 20.4;
 //   100 steps of the violent 256x128x128 box (440 to 2848) 31.6 on average and 41 at most / 27.8 and 134 /
-//   26.7 and 51.
-// The step, from fields out of bounds in every sweep: 64x32x32 (855) 79 / 75 / 72, (7.9 k) 98 / 390 / 95,
-//   64x64x32 (1.8 k) 98 / 157 / 84, (62 k, half of all) 103 / 1366 / 138, 256x128x128 (63 k) 638 / 3897 / 588,
-//   (1.9 M) 1730 / 40050 / 1778, polyhedra 64x32x32 (3.8 k) 133 / 473 / 139, (15 k) 65 / 906 / 76.
+//   25.8 and 48.
+// The step, from fields out of bounds in every sweep: 64x32x32 (855) 79 / 75 / 70, (7.9 k) 98 / 390 / 90,
+//   64x64x32 (1.8 k) 98 / 157 / 81, (62 k, half of all) 103 / 1366 / 138, 256x128x128 (63 k) 638 / 3897 / 552,
+//   (1.9 M) 1730 / 40050 / 1782, polyhedra 64x32x32 (3.8 k) 133 / 473 / 133, (15 k) 65 / 906 / 75.
 // The work-groups, 32 / 64 / 128: 128x64x64 (68 k) 326 / 325 / 305, 256x128x128 (1.9 M) 2464 / 1901 / 1778, calm,
 // where they leave at once, +0.2 / +0.4 / +1; polyhedra 128x64x64 (202 k cells, 111 k) 272 / 218 / 200, but not more
 // than 64 for their half-sized groups below 2^18 cells, where 128 cost as much in calm steps.  Four groups or fewer
