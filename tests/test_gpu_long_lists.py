@@ -3,7 +3,7 @@ plans do that share such lists between work-groups at the same time.
 
 The times are held against a step of the same mesh as an ensemble of one member, whose sweeps are launches on the
 whole grid, best of five each.  Bounds of 3 for the step and 12 for the adjoint (a traced step, sweeps forwards and
-back): a work-group that walks such lists alone takes more than 10 and 50 times the ensemble's step, sharing them
+back): a work-group that walks such lists alone takes some 10 and 50 times the ensemble's step, sharing them
 some 1.1 and 3 times."""
 import numpy as np
 import pytest
